@@ -9,7 +9,7 @@ namespace oq {
 // Event-timing kind of the packed linear; it follows the kinds of ProfKind.
 constexpr int PK_PACKED_LINEAR = 9;
 
-// Largest input width the packed linear takes (one token's staged row must fit LDS).
+// Largest input width the packed linear takes.
 constexpr int64_t PACKED_MAX_C_IN = 65536;
 
 // codes [c_out, c_in] u8 -> packed [c_out, c_in * bits / 8]: each row one
@@ -23,5 +23,21 @@ hipError_t packed_linear(const uint16_t* X, int64_t n_tok, int64_t c_in, const u
                          int bits, int64_t group, const float* h, const float* z,
                          const float* bias, int64_t c_out, void* Y, bool y_bf16,
                          hipStream_t stream);
+
+// Everything a launch of the packed linear needs besides its tokens.
+struct LinArgs {
+  int64_t c_in;
+  const uint32_t* packed;
+  int ng;
+  uint32_t group_inv;
+  const float *h, *z, *bias;
+  int64_t c_out;
+  bool y_bf16;
+  hipStream_t stream;
+};
+
+// The linear at one code width (packed_linear_b*.hip).
+template <int BITS>
+hipError_t linear_bits(const LinArgs& a, int64_t group, const uint16_t* X, int64_t n_tok, void* Y);
 
 }  // namespace oq

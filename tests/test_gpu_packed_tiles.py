@@ -1,0 +1,67 @@
+"""Packed linear: the edges of its kernels' tiles, against the oracle.
+
+Up to 96 tokens go in launches of at most 32 (4 tokens kept in LDS, 16 or 32
+staged per block), more through the tiled kernel (64 tokens x 128 outputs).
+Blocks of 128 channels hold one, two or four parts by the group size; inputs
+that are no multiple of 128 channels take dword copies and a short last block.
+The tolerance is the one derived for the packed linear: exact products, every
+rounding at most 2^-24 of a partial sum bounded by sum |x| (256 + q + |z|) h.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle.packed import pack_codes as o_pack, packed_linear as o_linear
+from paper_2308_13137_amd import oq
+from tests.test_gpu_packed import bound, make_linear, to_dev
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # bits, n_tok, c_out, c_in, group, bias, out dtype
+    (4, 97, 129, 256, 128, True, torch.float32),       # first tiled size, ragged both ways
+    (4, 128, 128, 384, 128, False, torch.bfloat16),    # whole tiles, odd number of blocks
+    (3, 130, 257, 640, 64, True, torch.float32),       # two parts per block
+    (2, 100, 40, 288, 96, False, torch.float32),       # 32-channel parts, short last block
+    (5, 193, 33, 160, 32, True, torch.bfloat16),
+    (6, 97, 130, 4096, 4096, False, torch.float32),    # one group per row
+    (7, 111, 1, 32, 32, True, torch.float32),
+    (4, 4, 17, 96, 32, True, torch.float32),           # dword copies, K shorter than the waves
+    (2, 3, 50, 2080, 32, False, torch.float32),        # 65 runs: short last block
+    (3, 16, 31, 2080, 160, True, torch.float32),
+    (7, 32, 33, 1056, 96, True, torch.bfloat16),       # wide codes: 32 tokens as 16 + 16
+    (4, 32, 48, 1152, 64, True, torch.float32),        # one launch of 32, two parts
+    (2, 31, 17, 2304, 128, False, torch.float32),
+    (6, 17, 40, 512, 256, False, torch.float32),       # groups of two blocks
+    (2, 4, 4112, 1280, 64, True, torch.float32),       # two row tiles, ragged last one
+    (4, 2, 16400, 256, 128, True, torch.float32),
+    (5, 5, 12304, 384, 32, False, torch.float32),
+    (4, 4, 70, 22016, 128, False, torch.float32),      # 4 tokens past what LDS keeps
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"b{c[0]}_t{c[1]}_{c[2]}x{c[3]}_g{c[4]}" for c in CASES])
+def test_packed_linear_tile_edges(case):
+    bits, n_tok, c_out, c_in, group, bias, odt = case
+    q, h, z, X, B = make_linear(900 + CASES.index(case), bits, n_tok, c_out, c_in, group, bias, 0)
+    P = o_pack(q, bits)
+    ref = o_linear(X, P, bits, group, h, z, B)
+    Y = oq.packed_linear(to_dev(X, torch.bfloat16), to_dev(P), bits, group, to_dev(h), to_dev(z),
+                         None if B is None else to_dev(B), out_dtype=odt)
+    torch.cuda.synchronize()
+    tol = bound(q, h, z, X, group)
+    if odt == torch.bfloat16:
+        tol = tol + np.abs(ref) * 2.0 ** -8
+    assert np.all(np.abs(Y.float().cpu().numpy().astype(np.float64) - ref) <= tol)
+
+
+def test_a_row_of_nan_steps_leaves_the_others_alone():
+    # reads past a row's end (short last block) meet the next row's step size
+    q, h, z, X, _ = make_linear(77, 4, 3, 20, 160, 32, False, 0)
+    h2 = h.copy()
+    h2[7] = np.nan
+    a, b = (oq.packed_linear(to_dev(X, torch.bfloat16), to_dev(o_pack(q, 4)), 4, 32, to_dev(v), to_dev(z))
+            for v in (h, h2))
+    torch.cuda.synchronize()
+    keep = [o for o in range(20) if o != 7]
+    assert torch.equal(a[:, keep], b[:, keep]) and torch.isnan(b[:, 7]).all()
