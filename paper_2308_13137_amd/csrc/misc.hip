@@ -71,6 +71,14 @@ __global__ __launch_bounds__(256) void let_fold_kernel(const TW* __restrict__ W,
   if (lane == 0 && Bt) Bt[o] = float(acc + (B ? double(B[o]) : 0.0));
 }
 
+// Without delta a folded bias is the bias itself (0 without one): the weights
+// are not read.  One row of workgroups per linear.
+__global__ __launch_bounds__(256) void bias_copy_kernel(BiasList L) {
+  const int l = blockIdx.y;
+  for (int64_t o = int64_t(blockIdx.x) * 256 + threadIdx.x; o < L.len[l]; o += int64_t(gridDim.x) * 256)
+    L.out[l][o] = 0.0f + (L.b[l] ? L.b[l][o] : 0.0f);
+}
+
 // ------------------------------------------------------------------ LET absorption
 // Folds a site's LET into the op that produces its input: row c of P [C, n]
 // (a normalisation's gain is n = 1, a previous linear's weight has its output
@@ -401,6 +409,15 @@ hipError_t let_fold(const void* W, bool w_bf16, const float* B, int64_t c_out, i
   } else {
     if (wt_bf16) go(float{}, uint16_t{}); else go(float{}, float{});
   }
+  return hipGetLastError();
+}
+
+hipError_t bias_copy(const BiasList& L, hipStream_t st) {
+  if (L.n <= 0) return hipSuccess;
+  int64_t most = 0;
+  for (int l = 0; l < L.n; ++l) most = std::max(most, L.len[l]);
+  hipLaunchKernelGGL(bias_copy_kernel, dim3(unsigned(std::min<int64_t>((most + 255) / 256, 64)), unsigned(L.n)),
+                     dim3(256), 0, st, L);
   return hipGetLastError();
 }
 

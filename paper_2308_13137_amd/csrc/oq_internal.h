@@ -113,6 +113,12 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
                    const float* gl, const float* bl, int bits, int64_t group, void* W_dq,
                    bool dq_bf16, uint8_t* codes, float* h, float* z, hipStream_t st,
                    float4* gstat = nullptr, int quant = 0);
+// LWC forward straight to the deployed bit strings (bits 2..7, c_in a multiple
+// of 32), with h and z, where lwc_pack_supported.
+bool lwc_pack_supported(int64_t c_in, int64_t group, bool has_s, int quant);
+hipError_t lwc_fwd_pack(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, const float* s,
+                        const float* gl, const float* bl, int bits, int64_t group, uint8_t* packed,
+                        float* h, float* z, hipStream_t st);
 // LWC backward.  When ds_parts != nullptr each block writes one partial row
 // [c_in] of sum_o dW~[o,c]*W[o,c] into ds_parts; the number of rows written is
 // lwc_bwd_nparts(c_out).
@@ -145,6 +151,14 @@ hipError_t transpose(const void* in, int64_t rows, int64_t cols, int64_t ld_in, 
 hipError_t let_fold(const void* W, bool w_bf16, const float* B, int64_t c_out, int64_t c_in,
                     const float* s, const float* delta, void* Wt, bool wt_bf16, float* Bt,
                     hipStream_t st);
+// Biases without a fold (no delta): out[l][0..n[l]) = B[l] or 0, one launch.
+struct BiasList {
+  int n;
+  const float* b[16];
+  float* out[16];
+  int64_t len[16];
+};
+hipError_t bias_copy(const BiasList& L, hipStream_t st);
 // LET absorbed into the producer of a site's input: Pout[c,:] = P[c,:]*(1/s[c]),
 // bout[c] = (b[c] - delta[c])*(1/s[c]); P is [C, n] (n = 1 for a norm gain).
 hipError_t let_absorb(const void* P, bool p_bf16, const float* b, int64_t C, int64_t n,

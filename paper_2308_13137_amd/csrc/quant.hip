@@ -103,6 +103,70 @@ struct Chunk8 {
   }
 };
 
+// ------------------------------------------------------------------ packed codes
+// Eight codes per lane into the deployed bit string (code j of a row at bits
+// j BITS ..): chunk c of the matrix takes bytes c BITS .. + BITS - 1.  4-bit
+// chunks are a dword, 2-bit ones a half-word; otherwise the four lanes of an
+// aligned quad exchange their chunks and share the run's BITS dwords.  The
+// matrix's chunks come in whole quads (c_in a multiple of 32), so a quad is
+// active or inactive as a whole.
+template <int BITS>
+OQ_DEV void store8_packed(uint8_t* packed, int64_t c, const float q[8]) {
+  uint64_t v = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v |= uint64_t(uint32_t(q[e]) & ((1u << BITS) - 1)) << (BITS * e);
+  if constexpr (BITS == 4) {
+    reinterpret_cast<uint32_t*>(packed)[c] = uint32_t(v);
+  } else if constexpr (BITS == 2) {
+    reinterpret_cast<uint16_t*>(packed)[c] = uint16_t(v);
+  } else {
+    uint64_t w[4];
+    const int lo = int(uint32_t(v)), hi = int(uint32_t(v >> 32));
+    auto join = [](int l, int h) { return uint64_t(uint32_t(l)) | uint64_t(uint32_t(h)) << 32; };
+    w[0] = join(__builtin_amdgcn_update_dpp(0, lo, 0x00, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, hi, 0x00, 0xF, 0xF, false));
+    w[1] = join(__builtin_amdgcn_update_dpp(0, lo, 0x55, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, hi, 0x55, 0xF, 0xF, false));
+    w[2] = join(__builtin_amdgcn_update_dpp(0, lo, 0xAA, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, hi, 0xAA, 0xF, 0xF, false));
+    w[3] = join(__builtin_amdgcn_update_dpp(0, lo, 0xFF, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, hi, 0xFF, 0xF, 0xF, false));
+    uint32_t d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < BITS; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int at = 32 * k - 8 * BITS * j;              // first bit of chunk j in dword k
+        if (at >= 0 && at < 8 * BITS) d[k] |= uint32_t(w[j] >> at);
+        if (at < 0 && at > -32) d[k] |= uint32_t(w[j] << -at);
+      }
+    const int l = int(c & 3);
+    uint32_t* run = reinterpret_cast<uint32_t*>(packed) + (c >> 2) * BITS;
+    run[l] = l == 0 ? d[0] : l == 1 ? d[1] : l == 2 ? d[2] : d[3];
+    if (4 + l < BITS) run[4 + l] = l == 0 ? d[4] : l == 1 ? d[5] : d[6];
+  }
+}
+// (3-bit runs have three dwords: the quad's last lane must not store)
+template <>
+OQ_DEV void store8_packed<3>(uint8_t* packed, int64_t c, const float q[8]) {
+  uint32_t v = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v |= (uint32_t(q[e]) & 7u) << (3 * e);
+  const uint32_t n = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x39, 0xF, 0xF, false));   // the next lane's
+  const int l = int(c & 3);
+  // dword l holds bits 8 l .. of this chunk's 24 and the next chunk's first 8 l + 8
+  if (l < 3) reinterpret_cast<uint32_t*>(packed)[(c >> 2) * 3 + l] = (v >> (8 * l)) | (n << (24 - 8 * l));
+}
+OQ_DEV void store8_packed(uint8_t* packed, int64_t c, const float q[8], int bits) {
+  switch (bits) {
+    case 2: store8_packed<2>(packed, c, q); break;
+    case 3: store8_packed<3>(packed, c, q); break;
+    case 4: store8_packed<4>(packed, c, q); break;
+    case 5: store8_packed<5>(packed, c, q); break;
+    case 6: store8_packed<6>(packed, c, q); break;
+    default: store8_packed<7>(packed, c, q); break;
+  }
+}
+
+// What the LWC forward writes of the codes: nothing, one byte each, or packed.
+enum CodeOut { CODES_NONE = 0, CODES_U8 = 1, CODES_PACKED = 2 };
+
 // ------------------------------------------------------------------ LWC forward
 template <typename TW, typename TQ, int KC, bool WHOLE_ROW>
 __global__ __launch_bounds__(NT) void lwc_fwd_kernel(
@@ -515,7 +579,7 @@ OQ_DEV void load_chunk(const TW* p, float (&x)[8]) {
   }
 }
 
-template <typename TW, typename TQ, int G, bool CODES>
+template <typename TW, typename TQ, int G, int CODES>
 __global__ __launch_bounds__(NT) void lwc_fwd_coal_kernel(
     const TW* __restrict__ W, int64_t nchunk, const float* __restrict__ gl,
     const float* __restrict__ bl, int bits, TQ* __restrict__ wdq, uint8_t* __restrict__ codes,
@@ -589,11 +653,12 @@ __global__ __launch_bounds__(NT) void lwc_fwd_coal_kernel(
       for (int e = 0; e < 8; ++e) {
         const float tq = __builtin_amdgcn_fmed3f(rintf(x[u][e] * ru), lo, hi);
         d[e] = tq * hu;
-        if constexpr (CODES) q[e] = tq + zu;
+        if constexpr (CODES != CODES_NONE) q[e] = tq + zu;
       }
       if (c < nchunk) {
         if (wdq) store8(wdq + 8 * c, d);
-        if constexpr (CODES) store8_codes(codes + 8 * c, q);
+        if constexpr (CODES == CODES_U8) store8_codes(codes + 8 * c, q);
+        if constexpr (CODES == CODES_PACKED) store8_packed(codes, c, q, bits);
       }
     }
   }
@@ -854,7 +919,7 @@ __global__ __launch_bounds__(NT) void act_fwd_row_kernel(
 // LET's s is staged in LDS once per workgroup as float4 slots [k][half][lane]
 // (conflict-free 128-bit reads).  Same Eq. 2 arithmetic as lwc_fwd_kernel:
 // the clamp is a median of three on rint(u) (q - z stays an exact integer).
-template <typename TW, typename TQ, int CH, bool CODES>
+template <typename TW, typename TQ, int CH, int CODES>
 __global__ __launch_bounds__(NT) void lwc_fwd_row_kernel(
     const TW* __restrict__ W, int64_t c_out, int64_t c_in, const float* __restrict__ s,
     const float* __restrict__ gl, const float* __restrict__ bl, int bits, TQ* __restrict__ wdq,
@@ -935,7 +1000,8 @@ __global__ __launch_bounds__(NT) void lwc_fwd_row_kernel(
         q[e] = tq + p.z;
       }
       if (wdq) store8(wdq + row * c_in + 8 * j, d);
-      if constexpr (CODES) store8_codes(codes + row * c_in + 8 * j, q);
+      if constexpr (CODES == CODES_U8) store8_codes(codes + row * c_in + 8 * j, q);
+      if constexpr (CODES == CODES_PACKED) store8_packed(codes, row * nch + j, q, bits);
     }
     if (lane == 0) {
       if (hout) hout[row] = p.h;
@@ -1328,11 +1394,11 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
       using TQ = decltype(tq);
       constexpr int Gc = decltype(gc)::value;
       if (codes)
-        hipLaunchKernelGGL((lwc_fwd_coal_kernel<TW, TQ, Gc, true>), grid, dim3(NT), 0, st,
+        hipLaunchKernelGGL((lwc_fwd_coal_kernel<TW, TQ, Gc, CODES_U8>), grid, dim3(NT), 0, st,
                            static_cast<const TW*>(W), nchunk, gl, bl, bits, static_cast<TQ*>(W_dq),
                            codes, h, z, gstat);
       else
-        hipLaunchKernelGGL((lwc_fwd_coal_kernel<TW, TQ, Gc, false>), grid, dim3(NT), 0, st,
+        hipLaunchKernelGGL((lwc_fwd_coal_kernel<TW, TQ, Gc, CODES_NONE>), grid, dim3(NT), 0, st,
                            static_cast<const TW*>(W), nchunk, gl, bl, bits, static_cast<TQ*>(W_dq),
                            codes, h, z, gstat);
     };
@@ -1363,12 +1429,12 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
       using TQ = decltype(tq);
       constexpr int CHc = decltype(chc)::value;
       if (codes) {
-        auto* k = lwc_fwd_row_kernel<TW, TQ, CHc, true>;
+        auto* k = lwc_fwd_row_kernel<TW, TQ, CHc, CODES_U8>;
         const dim3 grid(unsigned(std::min<int64_t>(want, resident_blocks((const void*)k, lds))));
         hipLaunchKernelGGL(k, grid, dim3(NT), lds, st, static_cast<const TW*>(W), c_out, c_in, s,
                            gl, bl, bits, static_cast<TQ*>(W_dq), codes, h, z);
       } else {
-        auto* k = lwc_fwd_row_kernel<TW, TQ, CHc, false>;
+        auto* k = lwc_fwd_row_kernel<TW, TQ, CHc, CODES_NONE>;
         const dim3 grid(unsigned(std::min<int64_t>(want, resident_blocks((const void*)k, lds))));
         hipLaunchKernelGGL(k, grid, dim3(NT), lds, st, static_cast<const TW*>(W), c_out, c_in, s,
                            gl, bl, bits, static_cast<TQ*>(W_dq), codes, h, z);
@@ -1413,6 +1479,65 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
   if (w_bf16) e = dq_bf16 ? by_wr(uint16_t{}, uint16_t{}) : by_wr(uint16_t{}, float{});
   else e = dq_bf16 ? by_wr(float{}, uint16_t{}) : by_wr(float{}, float{});
   if (e != hipSuccess) return e;
+  return hipGetLastError();
+}
+
+// The codes packed as they are formed (W^ is not wanted), where the kernels
+// that walk whole rows or small groups without s take the shape.
+bool lwc_pack_supported(int64_t c_in, int64_t group, bool has_s, int quant) {
+  if (quant != WQ_LWC || c_in % 32) return false;
+  return (small_group(group) && !has_s) || (group == c_in && (c_in / 8 + 63) / 64 <= 32);
+}
+
+hipError_t lwc_fwd_pack(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, const float* s,
+                        const float* gl, const float* bl, int bits, int64_t group, uint8_t* packed,
+                        float* h, float* z, hipStream_t st) {
+  if (bits < 2 || bits > 7 || !lwc_pack_supported(c_in, group, s != nullptr, WQ_LWC)) return hipErrorInvalidValue;
+  if (c_out <= 0) return hipSuccess;
+  if (small_group(group) && !s) {
+    const int64_t nchunk = c_out * c_in / 8;
+    const int64_t waves = std::min<int64_t>((nchunk + 511) / 512, 256 * 32);
+    const dim3 grid(unsigned((waves * 64 + NT - 1) / NT));
+    auto go = [&](auto tw, auto gc) {
+      using TW = decltype(tw);
+      hipLaunchKernelGGL((lwc_fwd_coal_kernel<TW, float, decltype(gc)::value, CODES_PACKED>), grid, dim3(NT), 0, st,
+                         static_cast<const TW*>(W), nchunk, gl, bl, bits, static_cast<float*>(nullptr), packed,
+                         h, z, static_cast<float4*>(nullptr));
+    };
+    auto by_g = [&](auto tw) {
+      switch (group / 8) {
+        case 1: go(tw, std::integral_constant<int, 1>{}); break;
+        case 2: go(tw, std::integral_constant<int, 2>{}); break;
+        case 4: go(tw, std::integral_constant<int, 4>{}); break;
+        case 8: go(tw, std::integral_constant<int, 8>{}); break;
+        case 16: go(tw, std::integral_constant<int, 16>{}); break;
+        case 32: go(tw, std::integral_constant<int, 32>{}); break;
+        default: go(tw, std::integral_constant<int, 64>{}); break;
+      }
+    };
+    if (w_bf16) by_g(uint16_t{}); else by_g(float{});
+    return hipGetLastError();
+  }
+  const int64_t per_lane = (c_in / 8 + 63) / 64;
+  const int ch = per_lane <= 8 ? 8 : per_lane <= 16 ? 16 : per_lane <= 24 ? 24 : 32;
+  const unsigned lds = s ? unsigned(ch) * 128u * 16u : 0u;
+  const int64_t want = (c_out + NT / 64 - 1) / (NT / 64);
+  auto run = [&](auto tw, auto chc) {
+    using TW = decltype(tw);
+    auto* k = lwc_fwd_row_kernel<TW, float, decltype(chc)::value, CODES_PACKED>;
+    const dim3 grid(unsigned(std::min<int64_t>(want, resident_blocks((const void*)k, lds))));
+    hipLaunchKernelGGL(k, grid, dim3(NT), lds, st, static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits,
+                       static_cast<float*>(nullptr), packed, h, z);
+  };
+  auto by_ch = [&](auto tw) {
+    switch (ch) {
+      case 8: run(tw, std::integral_constant<int, 8>{}); break;
+      case 16: run(tw, std::integral_constant<int, 16>{}); break;
+      case 24: run(tw, std::integral_constant<int, 24>{}); break;
+      default: run(tw, std::integral_constant<int, 32>{}); break;
+    }
+  };
+  if (w_bf16) by_ch(uint16_t{}); else by_ch(float{});
   return hipGetLastError();
 }
 
