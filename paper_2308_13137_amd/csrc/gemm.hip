@@ -1012,12 +1012,16 @@ OQ_DEV void half_sched(f32x4_t (&acc)[8][4], const bf16x8_t (&au)[8], const bf16
 
 OQ_DEV void wait_vm4() { asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); }
 
-template <class Epi, bool AMN, bool BMN>
+template <class Epi, bool AMN, bool BMN, bool KT = false>
 __global__ __launch_bounds__(NTHR8, 1) void gemm_bf16_w8_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int64_t M, int64_t N,
-    int64_t K, int64_t lda, int64_t ldb, int tiles_m, int tiles_n, Epi epi) {
+    int64_t K, int64_t lda, int64_t ldb, int tiles_m, int tiles_n, int64_t kvalid, Epi epi) {
   // With a K split (grid = tiles x splits) each workgroup runs K of the
   // whole and writes its own partial output (Epi::split).
+  // KT: the MN-major B holds fewer than K rows (kvalid, past the start of the
+  // last stage): the last stage re-reads row kvalid - 1 for the others, which
+  // meet zero columns of A.  (A variant of its own: the offsets' update costs
+  // the others registers that they spill.)
   // B stages at 0, 32 and 64 KiB, A stages at 96 and 128 KiB
   __shared__ uint4 lds[5 * 32768 / 16];
 
@@ -1048,6 +1052,17 @@ __global__ __launch_bounds__(NTHR8, 1) void gemm_bf16_w8_kernel(
   uint32_t aoff[4], boff[4];
   dma_plan<AMN>(aoff, m0, M, lda, wave, lane);
   dma_plan<BMN>(boff, n0, N, ldb, wave, lane);
+  const int64_t brows_l = KT ? kvalid - (ks * K + int64_t(nk - 1) * BK) : BK;
+  const int brows = brows_l < BK ? int(brows_l) : BK;
+  auto clamp_b = [&](int stage) {              // before the copies of `stage`
+    if (KT && stage == nk - 1 && brows < BK) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * i + 2 * wave + (lane >> 5);
+        if (r >= brows) boff[i] -= uint32_t(2 * (r - (brows - 1)) * ldb);
+      }
+    }
+  };
   const uint32_t lds0 = lds_addr_of(&lds[0]);
   lds_cchar* lbase = (lds_cchar*)(&lds[0]);
   const int wm = wave >> 2, wn = wave & 3;
@@ -1067,6 +1082,7 @@ __global__ __launch_bounds__(NTHR8, 1) void gemm_bf16_w8_kernel(
   // stage 0 (A then B), then stage 1 in flight
 #pragma unroll
   for (int i = 0; i < 4; ++i) dma16_s(At, aoff[i], a_lds(0) + (8 * i + wave) * 1024);
+  clamp_b(0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) dma16_s(Bt, boff[i], b_lds(0) + (8 * i + wave) * 1024);
   wait_vm0();
@@ -1076,6 +1092,7 @@ __global__ __launch_bounds__(NTHR8, 1) void gemm_bf16_w8_kernel(
   if (nk > 1) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) dma16_s(At + astep, aoff[i], a_lds(1) + (8 * i + wave) * 1024);
+    clamp_b(1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) dma16_s(Bt + bstep, boff[i], b_lds(1) + (8 * i + wave) * 1024);
   }
@@ -1086,6 +1103,7 @@ __global__ __launch_bounds__(NTHR8, 1) void gemm_bf16_w8_kernel(
   // waits for stage kt + 1 with B of stage kt + 2 still in flight.
   int kt = 0;
   for (; kt + 2 < nk; ++kt) {
+    clamp_b(kt + 2);
     half_sched<AMN, BMN, true>(acc, a0, b0, a_tile(kt), b_tile(kt), 1, wm, wn, lane, a1, b1,
                                Bt + (kt + 2) * bstep, boff, b_lds(kt + 2), wave);
     wait_vm4();
@@ -1270,11 +1288,16 @@ bool w8_ok(bool amn, bool bmn, int64_t M, int64_t N, int64_t K, int64_t lda, int
 
 template <class Epi, bool AMN, bool BMN>
 void launch_w8(const void* A, const void* B, int64_t M, int64_t N, int64_t K, int64_t lda,
-               int64_t ldb, int64_t tm, int64_t tn, Epi epi, hipStream_t st, int splits = 1) {
-  hipLaunchKernelGGL((gemm_bf16_w8_kernel<Epi, AMN, BMN>), dim3(unsigned(tm * tn * splits)),
+               int64_t ldb, int64_t tm, int64_t tn, Epi epi, hipStream_t st, int splits = 1,
+               int64_t kvalid = 0) {
+  auto k = gemm_bf16_w8_kernel<Epi, AMN, BMN>;
+  if constexpr (BMN && !AMN) {
+    if (kvalid && kvalid < K * splits) k = gemm_bf16_w8_kernel<Epi, AMN, BMN, true>;
+  }
+  hipLaunchKernelGGL(k, dim3(unsigned(tm * tn * splits)),
                      dim3(NTHR8), 0,
                      st, static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), M, N, K,
-                     lda, ldb, int(tm), int(tn), epi);
+                     lda, ldb, int(tm), int(tn), kvalid, epi);
 }
 
 // amn / bmn: operand stored MN-major (A as [K, M], B as [K, N]); bf16 only,
@@ -1282,8 +1305,10 @@ void launch_w8(const void* A, const void* B, int64_t M, int64_t N, int64_t K, in
 template <class Epi>
 hipError_t launch(const void* A, const void* B, bool bf16, int64_t M, int64_t N, int64_t K,
                   int64_t lda, int64_t ldb, Epi epi, hipStream_t st, bool amn = false,
-                  bool bmn = false, int splits = 1) {
+                  bool bmn = false, int splits = 1, int64_t kvalid = 0) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  // a short B only as the MN-major operand, ending within the last stage
+  if (kvalid && (amn || !bmn || kvalid > K * splits || kvalid <= K * splits - BK)) return hipErrorInvalidValue;
   if (bf16) {
     const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
     if (tm * tn * splits > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
@@ -1294,7 +1319,7 @@ hipError_t launch(const void* A, const void* B, bool bf16, int64_t M, int64_t N,
         if (amn && bmn)
           launch_w8<Epi, true, true>(A, B, M, N, K, lda, ldb, tm, tn, epi, st, splits);
         else if (bmn)
-          launch_w8<Epi, false, true>(A, B, M, N, K, lda, ldb, tm, tn, epi, st, splits);
+          launch_w8<Epi, false, true>(A, B, M, N, K, lda, ldb, tm, tn, epi, st, splits, kvalid);
         else
           launch_w8<Epi, true, false>(A, B, M, N, K, lda, ldb, tm, tn, epi, st, splits);
       } else {
@@ -1364,14 +1389,14 @@ int gemm_mn_splits(bool a_mn, bool b_mn, int64_t M, int64_t N, int64_t K, int64_
 
 hipError_t gemm_f32out_mn(const void* A, bool a_mn, const void* B, bool b_mn, int64_t M,
                           int64_t N, int64_t K, int64_t lda, int64_t ldb, float* C, int64_t ldc,
-                          hipStream_t st, int splits, int64_t split_stride) {
+                          hipStream_t st, int splits, int64_t split_stride, int64_t kvalid) {
   if (splits < 1 || K % splits) return hipErrorInvalidValue;
   const int64_t ks = K / splits;
   if (splits > 1 && !w8_ok(a_mn, b_mn, M, N, ks, lda, ldb)) return hipErrorInvalidValue;
   const bool vec = ldc % 8 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0 &&
                    split_stride % 8 == 0;
   return launch(A, B, true, M, N, ks, lda, ldb, EpiF32{C, ldc, vec, split_stride}, st, a_mn,
-                b_mn, splits);
+                b_mn, splits, kvalid);
 }
 
 bool gemm_wgrad_lwc_supported(int64_t M, int64_t C, int64_t K, int group) {
@@ -1380,15 +1405,16 @@ bool gemm_wgrad_lwc_supported(int64_t M, int64_t C, int64_t K, int group) {
 }
 
 hipError_t gemm_wgrad_lwc(const void* dyT, const void* x, int64_t M, int64_t C, int64_t K,
-                          int64_t lda, int64_t ldb, const LwcArgs& la, hipStream_t st) {
+                          int64_t lda, int64_t ldb, const LwcArgs& la, hipStream_t st, int64_t kvalid) {
   if (!gemm_wgrad_lwc_supported(M, C, K, la.group) || lda != K || ldb != C || la.C != C ||
-      la.ng != C / la.group || la.nseg < 1 || la.nseg > MAX_SEG)
+      la.ng != C / la.group || la.nseg < 1 || la.nseg > MAX_SEG || kvalid > K || kvalid <= K - BK)
     return hipErrorInvalidValue;
   auto go = [&](auto gc) {
     constexpr int Gc = decltype(gc)::value;
     const int64_t tm = (M + BM - 1) / BM, tn = (C + BN - 1) / BN;
     if (tm * tn > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    launch_w8<EpiLwc<Gc>, false, true>(dyT, x, M, C, K, lda, ldb, tm, tn, EpiLwc<Gc>{la}, st);
+    launch_w8<EpiLwc<Gc>, false, true>(dyT, x, M, C, K, lda, ldb, tm, tn, EpiLwc<Gc>{la}, st, 1,
+                                      kvalid);
     return hipGetLastError();
   };
   switch (la.group / 8) {

@@ -79,6 +79,25 @@ __global__ __launch_bounds__(256) void bias_copy_kernel(BiasList L) {
     L.out[l][o] = 0.0f + (L.b[l] ? L.b[l][o] : 0.0f);
 }
 
+// The zeros that round a product's K up to whole stages: 16-byte stores, the
+// edge of each row first, then the rows past the end, then b.
+__global__ __launch_bounds__(256) void pad_zero_kernel(uint4* a, int64_t rows, int64_t cols, int64_t tail,
+                                                       int64_t ld, int64_t edge, uint4* b, int64_t n_b) {
+  const int64_t n_edge = rows * edge, n = n_edge + tail + n_b;
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+    uint4* p;
+    if (i < n_edge) {
+      const int64_t r = i / edge;
+      p = a + r * ld + cols + (i - r * edge);
+    } else if (i < n_edge + tail) {
+      p = a + rows * ld + (i - n_edge);
+    } else {
+      p = b + (i - n_edge - tail);
+    }
+    *p = make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
 // ------------------------------------------------------------------ LET absorption
 // Folds a site's LET into the op that produces its input: row c of P [C, n]
 // (a normalisation's gain is n = 1, a previous linear's weight has its output
@@ -498,6 +517,17 @@ hipError_t row_partials(const float* psq, const float* pdy, int64_t M, int ntn, 
   if (M <= 0) return hipSuccess;
   hipLaunchKernelGGL(row_partials_kernel, dim3(unsigned((M + 3) / 4)), dim3(256), 0, st, psq, pdy,
                      M, ntn, rl, dbt);
+  return hipGetLastError();
+}
+
+hipError_t pad_zero(void* a, int64_t rows, int64_t cols, int64_t rows_p, int64_t cols_p, void* b, int64_t n_b,
+                    hipStream_t st) {
+  const int64_t edge = (cols_p - cols) / 8;
+  const int64_t n = rows * edge + (rows_p - rows) * cols_p / 8 + (b ? n_b / 8 : 0);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(pad_zero_kernel, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 1024))), dim3(256), 0, st,
+                     static_cast<uint4*>(a), rows, cols / 8, (rows_p - rows) * cols_p / 8, cols_p / 8, edge,
+                     static_cast<uint4*>(b), b ? n_b / 8 : 0);
   return hipGetLastError();
 }
 

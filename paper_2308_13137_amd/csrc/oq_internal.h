@@ -55,7 +55,9 @@ hipError_t gemm_nt_f32out(const void* A, const void* B, bool bf16, int64_t M, in
 // shapes qualify (K a multiple of 64 and aligned strides).  With splits > 1
 // the K range is cut into that many equal parts (each a multiple of 64) and
 // part s writes its own partial product at C + s * split_stride; the caller
-// sums the parts (sum_partials).
+// sums the parts (sum_partials).  kvalid (0 = K): an MN-major B holds only that
+// many rows, ending within the last stage of 64; A's columns from kvalid on
+// are zeros.
 bool gemm_mn_supported(bool a_mn, bool b_mn, int64_t M, int64_t N, int64_t K, int64_t lda,
                        int64_t ldb);
 // K-split count (1, 2, 4 or 8) for gemm_f32out_mn on an M x N output: the one
@@ -65,7 +67,8 @@ int gemm_mn_splits(bool a_mn, bool b_mn, int64_t M, int64_t N, int64_t K, int64_
                    int64_t ldb);
 hipError_t gemm_f32out_mn(const void* A, bool a_mn, const void* B, bool b_mn, int64_t M,
                           int64_t N, int64_t K, int64_t lda, int64_t ldb, float* C, int64_t ldc,
-                          hipStream_t st, int splits = 1, int64_t split_stride = 0);
+                          hipStream_t st, int splits = 1, int64_t split_stride = 0,
+                          int64_t kvalid = 0);
 hipError_t gemm_nt_store(const void* A, const void* B, bool bf16, int64_t M, int64_t N, int64_t K,
                          int64_t lda, int64_t ldb, void* C, bool c_bf16, int64_t ldc,
                          const float* bias, hipStream_t st);
@@ -98,9 +101,10 @@ struct LwcArgs {
   float qmax;
 };
 bool gemm_wgrad_lwc_supported(int64_t M, int64_t C, int64_t K, int group);
-// dY^T [M, K] K-contiguous (lda), X^ [K, C] read C-contiguous (ldb).
+// dY^T [M, K] K-contiguous (lda), X^ [kvalid, C] read C-contiguous (ldb), dY^T's
+// columns from kvalid on zeros.
 hipError_t gemm_wgrad_lwc(const void* dyT, const void* x, int64_t M, int64_t C, int64_t K,
-                          int64_t lda, int64_t ldb, const LwcArgs& la, hipStream_t st);
+                          int64_t lda, int64_t ldb, const LwcArgs& la, hipStream_t st, int64_t kvalid);
 
 // ---------------------------------------------------------------- quantisers
 // LWC forward on rows [0, c_out) of one weight.  Returns hipErrorInvalidValue
@@ -174,6 +178,11 @@ hipError_t wcolsum(const void* W, bool w_bf16, int64_t rows, int64_t cols, const
 hipError_t let_grad_finish(int64_t C, const float* s, const float* pw, int64_t npw,
                            const float* psx, const float* ps1, int64_t npa, const float* pb,
                            int64_t npb, float* d_s, float* d_delta, hipStream_t st);
+// Zeros around a [rows, cols] bf16 matrix in a [rows_p, cols_p] buffer (row
+// stride cols_p): columns cols .. of its rows and the rows past them; and
+// the n_b elements at b (nullptr: none).  All counts multiples of 8.
+hipError_t pad_zero(void* a, int64_t rows, int64_t cols, int64_t rows_p, int64_t cols_p, void* b, int64_t n_b,
+                    hipStream_t st);
 // Row sums of the forward partials: rl[m] = sum_j psq[m][j] (fp64), and
 // dbt[m] = sum_j pdy[m][j] when pdy != nullptr.
 hipError_t row_partials(const float* psq, const float* pdy, int64_t M, int ntn, double* rl,
