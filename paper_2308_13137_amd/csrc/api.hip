@@ -674,8 +674,11 @@ int64_t rows_pad(const SitePlan& p) { return p.let ? up64(p.M) : p.M; }
 // as stored (no transposes of the token-sized operands): bf16, any token count
 // and row count (a ragged one pads the workspace's own operands, and the
 // weight gradient re-reads the last row of an X that is the caller's).
+// Small fp32 products read the same operands as stored.
 bool direct_grads(const oq_block_desc* d, const SitePlan& p) {
-  if (d->dtype != OQ_BF16) return false;
+  if (d->dtype != OQ_BF16)
+    return gemm_f32_mn_supported(p.M, p.C, d->tokens, d->tokens, p.C) &&
+           (!p.let || gemm_f32_mn_supported(d->tokens, p.C, p.M, d->tokens, p.C));
   const int64_t T = d->tokens, Tp = up64(T);
   bool ok = gemm_mn_supported(false, true, p.M, p.C, Tp, Tp, p.C);
   if (p.let) ok = ok && gemm_mn_supported(true, true, T, p.C, up64(p.M), Tp, p.C);
@@ -685,14 +688,14 @@ bool direct_grads(const oq_block_desc* d, const SitePlan& p) {
 // The direct input gradient reads W^ through a transposed copy when the
 // tokens are many enough for the faster product to repay the copy.
 bool direct_wt_copy(const oq_block_desc* d, const SitePlan& p) {
-  return p.let && d->tokens >= 65536 && p.M % 64 == 0 && direct_grads(d, p) &&
+  return d->dtype == OQ_BF16 && p.let && d->tokens >= 65536 && p.M % 64 == 0 && direct_grads(d, p) &&
          gemm_mn_supported(true, false, d->tokens, p.C, p.M, up64(d->tokens), p.M);
 }
 
 // K-split count of the weight gradient (its K is the token count); only the
 // direct path splits.
 int wgrad_splits(const oq_block_desc* d, const SitePlan& p) {
-  if (!direct_grads(d, p)) return 1;
+  if (d->dtype != OQ_BF16 || !direct_grads(d, p)) return 1;
   const int64_t Tp = up64(d->tokens);
   return gemm_mn_splits(false, true, p.M, p.C, Tp, Tp, p.C);
 }
@@ -708,7 +711,8 @@ int fwd_splits(const oq_block_desc* d, const SitePlan& p) {
 // when that product is not split, the site has no LET, and every linear of it
 // shares one power-of-two group of at most 256 weights and one bit width.
 bool fused_lwc(const oq_block_desc* d, const SitePlan& p) {
-  if (p.let || !p.lwc_only || !direct_grads(d, p) || wgrad_splits(d, p) != 1) return false;
+  if (d->dtype != OQ_BF16 || p.let || !p.lwc_only || !direct_grads(d, p) || wgrad_splits(d, p) != 1)
+    return false;
   const int64_t g = d->lin_group[p.l0];
   for (int l = p.l0; l < p.l1; ++l)
     if (d->lin_group[l] != g || d->lin_bits[l] != d->lin_bits[p.l0]) return false;
@@ -802,11 +806,11 @@ struct SiteSizes {
 SiteSizes site_sizes(const oq_block_desc* d, const SitePlan& p) {
   const bool bf = d->dtype == OQ_BF16;
   const int64_t T = d->tokens;
-  const int ptn = gemm_part_tile_n(bf);
+  const int ptn = gemm_part_tile_n(bf, p.M, T, p.C);
   const int64_t ntn = (T + ptn - 1) / ptn;
   const bool direct = direct_grads(d, p);
   SiteSizes z;
-  const int64_t Tp = direct ? up64(T) : T, Mp = direct ? rows_pad(p) : p.M;
+  const int64_t Tp = direct && bf ? up64(T) : T, Mp = direct && bf ? rows_pad(p) : p.M;
   z.what = size_t(Mp * p.C);
   if (!direct) z.xhatT = size_t(T * p.C);
   z.dyT = size_t(Mp * Tp);
@@ -969,8 +973,6 @@ oq_status oq_block_calib_step(const oq_block_desc* d, const void* const* Y_fp_T,
   const bool bf = d->dtype == OQ_BF16;
   const size_t es = bf ? 2 : 4;
   const int64_t T = d->tokens;
-  const int ptn = gemm_part_tile_n(bf);
-  const int ntn = int((T + ptn - 1) / ptn);
   int64_t row_base = 0;
   LossArgs la{};
   la.nlin = d->n_linears;
@@ -981,8 +983,10 @@ oq_status oq_block_calib_step(const oq_block_desc* d, const void* const* Y_fp_T,
     const BlockWs& w = wsets[si];
     const int k = p.k;
     const int64_t C = p.C, M = p.M;
+    const int ptn = gemm_part_tile_n(bf, M, T, C);
+    const int ntn = int((T + ptn - 1) / ptn);
     const bool direct = direct_grads(d, p);
-    const int64_t Tp = direct ? up64(T) : T, Mp = direct ? rows_pad(p) : M;
+    const int64_t Tp = direct && bf ? up64(T) : T, Mp = direct && bf ? rows_pad(p) : M;
     const float* s = p.let ? prm->s[k] : nullptr;
     const float* dl = p.let ? prm->delta[k] : nullptr;
     // LET gradients (the input-gradient path) only for a trained LET; the
@@ -1113,6 +1117,8 @@ oq_status oq_block_calib_step(const oq_block_desc* d, const void* const* Y_fp_T,
         la.ng = int(ngs);
         la.qmax = float((1 << d->lin_bits[p.l0]) - 1);
         OQ_HIP(gemm_wgrad_lwc(w.dyT, xsrc, M, C, Tp, Tp, C, la, st, T), "wgrad gemm with LWC backward");
+      } else if (direct && !bf) {
+        OQ_HIP(gemm_f32_mn(w.dyT, false, xsrc, M, C, T, T, C, w.dW, C, st), "wgrad gemm");
       } else if (direct) {
         OQ_HIP(gemm_f32out_mn(w.dyT, false, xsrc, true, M, C, Tp, Tp, C, w.dW, C, st, S, M * C, T),
                "wgrad gemm");
@@ -1150,6 +1156,9 @@ oq_status oq_block_calib_step(const oq_block_desc* d, const void* const* Y_fp_T,
         ProfScope ps(PK_GEMM_DGRAD, st, 2.0 * double(M) * T * C);
         OQ_HIP(gemm_f32out_mn(w.dyT, true, w.whatT, false, T, C, M, Tp, M, w.dX, C, st),
                "dgrad gemm");
+      } else if (direct && !bf) {
+        ProfScope ps(PK_GEMM_DGRAD, st, 2.0 * double(M) * T * C);
+        OQ_HIP(gemm_f32_mn(w.dyT, true, w.what, T, C, M, T, C, w.dX, C, st), "dgrad gemm");
       } else if (direct) {
         // dX^ [T, C] = dY W^ with dY^T [M, T] and W^ [M, C] read as stored
         ProfScope ps(PK_GEMM_DGRAD, st, 2.0 * double(M) * T * C);

@@ -1275,6 +1275,120 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+// ------------------------------------------------------------------ fp32, few tiles
+// The fp32 workloads' matrices are small: with 64 x 64 tiles a 256 x 128 product
+// is 8 workgroups walking K through LDS and two barriers per 16 columns.  Here
+// every wave owns a 16 x 16 tile on v_mfma_f32_16x16x4_f32 (fp32 operands and
+// sums) and loads its operands straight into registers, the next 64 of K in
+// flight while these 64 compute: no LDS, no barriers, sixteen times the
+// workgroups.  Lane (f, i) (f = lane / 16, i =
+// lane % 16) takes k = 16 j + 4 f + e of row i of either side for instruction
+// (j, e): any order of the summed index serves.  K-major operands load 16
+// bytes of a row, MN-major ones ([K, M] or [K, N]) four k-rows' elements.
+// Rows and k past the end read zeros.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr int FS_K = 64;
+
+template <bool MN>
+struct SmallOperand {
+  rsrc_t r;
+  uint32_t off, step_j, step_e;                // bytes: this lane's first element, per j, per e
+  int k0;                                      // this lane's first k
+  OQ_DEV SmallOperand(const float* p, int64_t m0, int64_t M, int64_t K, int64_t ld, int lane) {
+    const int f = lane >> 4, i = lane & 15;
+    k0 = 4 * f;
+    if constexpr (MN) {
+      r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, uint32_t(K * ld * 4), 0x00027000);
+      off = m0 + i < M ? uint32_t((4 * f * ld + m0 + i) * 4) : 0x80000000u;
+      step_j = uint32_t(16 * ld * 4);
+      step_e = uint32_t(ld * 4);
+    } else {
+      const int64_t left = M - m0;
+      r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p + m0 * ld), 0,
+                                            uint32_t((left < 16 ? left : 16) * ld * 4), 0x00027000);
+      off = uint32_t((i * ld + 4 * f) * 4);
+      step_j = 64;
+      step_e = 0;
+    }
+  }
+  OQ_DEV void load(int kb, int K, float (&v)[4][4]) const {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = kb + 16 * j + k0 < K;    // K is a multiple of 4
+      const uint32_t o = off + uint32_t(kb / 16 + j) * step_j;
+      if constexpr (MN) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[j][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, in ? o + e * step_e : 0x80000000u, 0, 0));
+      } else {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const u4 q = __builtin_amdgcn_raw_buffer_load_b128(r, in ? o : 0x80000000u, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = __uint_as_float(q[e]);
+      }
+    }
+  }
+};
+
+template <class Epi, bool AMN, bool BMN>
+__global__ __launch_bounds__(64) void gemm_f32_small_kernel(const float* __restrict__ A,
+                                                            const float* __restrict__ B, int64_t M, int64_t N,
+                                                            int64_t K, int64_t lda, int64_t ldb, Epi epi) {
+  const int lane = threadIdx.x, f = lane >> 4, i = lane & 15;
+  const int64_t m0 = int64_t(blockIdx.y) * 16, n0 = int64_t(blockIdx.x) * 16;
+  const SmallOperand<AMN> a(A, m0, M, K, lda, lane);
+  const SmallOperand<BMN> b(B, n0, N, K, ldb, lane);
+  f32x4_t acc{0.f, 0.f, 0.f, 0.f};
+  float av[2][4][4], bv[2][4][4];
+  a.load(0, int(K), av[0]);
+  b.load(0, int(K), bv[0]);
+  for (int k = 0; k < int(K); k += 2 * FS_K) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      // (loads past K read nothing; products with zeros add nothing)
+      a.load(k + (h + 1) * FS_K, int(K), av[h ^ 1]);
+      b.load(k + (h + 1) * FS_K, int(K), bv[h ^ 1]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[h][j][e], bv[h][j][e], acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t m = m0 + 4 * f + r, n = n0 + i;
+    float sq = 0.f, sdy = 0.f;
+    if (m < M && n < N) {
+      const float v[8] = {acc[r], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const float2 c = epi.apply8(epi.row(m), n, v, 1);
+      sq = c.x;
+      sdy = c.y;
+    }
+    if constexpr (Epi::kRows) {
+      sq = group_sum<16>(sq);
+      sdy = group_sum<16>(sdy);
+      if (i == 0 && m < M) epi.finish(m, int(blockIdx.x), sq, sdy);
+    }
+  }
+}
+
+// Fewer than 256 tiles of 64 x 64 (less than one per compute unit): the wave
+// tiles.  Their operands are addressed in 31 bits.
+bool f32_small(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+  const int64_t tiles = ((M + F32_TILE - 1) / F32_TILE) * ((N + F32_TILE - 1) / F32_TILE);
+  const int64_t most = int64_t(1) << 29;
+  return tiles < 256 && K % 4 == 0 && lda % 4 == 0 && ldb % 4 == 0 && (M + 16) * lda < most && (N + 16) * ldb < most &&
+         (K + 128) * lda < most && (K + 128) * ldb < most;
+}
+
+template <class Epi, bool AMN, bool BMN>
+void launch_f32_small(const void* A, const void* B, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                      Epi epi, hipStream_t st) {
+  hipLaunchKernelGGL((gemm_f32_small_kernel<Epi, AMN, BMN>), dim3(unsigned((N + 15) / 16), unsigned((M + 15) / 16)),
+                     dim3(64), 0, st, static_cast<const float*>(A), static_cast<const float*>(B), M, N, K, lda, ldb,
+                     epi);
+}
+
 // The 8-wave kernel applies when K is a multiple of 64 and every operand
 // offset of a tile fits the kernel's 32-bit byte offsets.
 bool w8_ok(bool amn, bool bmn, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
@@ -1335,7 +1449,16 @@ hipError_t launch(const void* A, const void* B, bool bf16, int64_t M, int64_t N,
       return hipErrorInvalidValue;
     }
   } else {
-    if (amn || bmn || splits != 1) return hipErrorInvalidValue;
+    if (splits != 1) return hipErrorInvalidValue;
+    if (f32_small(M, N, K, lda, ldb)) {
+      if (!amn && !bmn) launch_f32_small<Epi, false, false>(A, B, M, N, K, lda, ldb, epi, st);
+      else if constexpr (!std::is_same<Epi, EpiF32>::value) return hipErrorInvalidValue;
+      else if (amn && bmn) launch_f32_small<Epi, true, true>(A, B, M, N, K, lda, ldb, epi, st);
+      else if (bmn) launch_f32_small<Epi, false, true>(A, B, M, N, K, lda, ldb, epi, st);
+      else return hipErrorInvalidValue;
+      return hipGetLastError();
+    }
+    if (amn || bmn) return hipErrorInvalidValue;
     const int64_t tm = (M + F32_TILE - 1) / F32_TILE, tn = (N + F32_TILE - 1) / F32_TILE;
     if (tm > 65535 || tn > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gemm_f32_kernel<Epi>, dim3(unsigned(tn), unsigned(tm)), dim3(256), 0, st,
@@ -1347,7 +1470,19 @@ hipError_t launch(const void* A, const void* B, bool bf16, int64_t M, int64_t N,
 
 }  // namespace
 
-int gemm_part_tile_n(bool bf16) { return bf16 ? BN : F32_TILE; }
+int gemm_part_tile_n(bool bf16, int64_t M, int64_t N, int64_t K) {
+  return bf16 ? BN : f32_small(M, N, K, K, K) ? 16 : F32_TILE;
+}
+
+bool gemm_f32_mn_supported(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+  return f32_small(M, N, K, lda, ldb);
+}
+
+hipError_t gemm_f32_mn(const void* A, bool a_mn, const void* B, int64_t M, int64_t N, int64_t K, int64_t lda,
+                       int64_t ldb, float* C, int64_t ldc, hipStream_t st) {
+  if (!f32_small(M, N, K, lda, ldb)) return hipErrorInvalidValue;
+  return launch(A, B, false, M, N, K, lda, ldb, EpiF32{C, ldc, false, 0}, st, a_mn, true);
+}
 
 hipError_t gemm_nt_f32out(const void* A, const void* B, bool bf16, int64_t M, int64_t N,
                           int64_t K, int64_t lda, int64_t ldb, float* C, int64_t ldc,
@@ -1486,7 +1621,9 @@ hipError_t gemm_nt_resid_split(const void* A, const void* B, int64_t M, int64_t 
 
 hipError_t gemm_nt_resid(const void* A, const void* B, bool bf16, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, ResidArgs ra, hipStream_t st) {
-  ra.ntn = int((N + gemm_part_tile_n(bf16) - 1) / gemm_part_tile_n(bf16));
+  const int ptn = gemm_part_tile_n(bf16, M, N, K);
+  if (!bf16 && (lda != K || ldb != K)) return hipErrorInvalidValue;   // the tile rule reads dense operands
+  ra.ntn = int((N + ptn - 1) / ptn);
   bool vec = ra.ld_yfp % 8 == 0 && ra.ld_dy % 8 == 0 &&
              (reinterpret_cast<uintptr_t>(ra.dy) & 15) == 0;
   for (int s = 0; s < ra.nseg; ++s) vec = vec && (reinterpret_cast<uintptr_t>(ra.yfp[s]) & 15) == 0;

@@ -44,8 +44,14 @@ struct ResidArgs {
   int ntn;                         // column tiles (set by the launcher)
 };
 
-// Column-tile width of the row partials written by the forward epilogue.
-int gemm_part_tile_n(bool bf16);
+// Column-tile width of the row partials written by the forward epilogue (fp32:
+// dense K-major operands).
+int gemm_part_tile_n(bool bf16, int64_t M, int64_t N, int64_t K);
+// fp32 C[M,N] = op(A) B with B [K, N] and A [M, K], or (a_mn) [K, M], read as
+// stored; only where few output tiles make it the wave-tile kernel's.
+bool gemm_f32_mn_supported(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb);
+hipError_t gemm_f32_mn(const void* A, bool a_mn, const void* B, int64_t M, int64_t N, int64_t K, int64_t lda,
+                       int64_t ldb, float* C, int64_t ldc, hipStream_t st);
 
 hipError_t gemm_nt_f32out(const void* A, const void* B, bool bf16, int64_t M, int64_t N, int64_t K,
                           int64_t lda, int64_t ldb, float* C, int64_t ldc, hipStream_t st);

@@ -53,3 +53,42 @@ def test_ragged_step_matches_oracle(case):
         g = g.cpu().numpy().astype(np.float64)
         assert normwise(g, r) <= 1e-3
         assert np.all(np.abs(g - r) <= 1e-2 * np.maximum(np.abs(r), 1e-2 * np.abs(r).max()))
+
+
+FP32 = [  # tokens, hidden, ffn, bits, group, LET, activation bits
+    (8, 64, 128, 4, 64, False, 16),              # less than one 16 x 16 tile of tokens
+    (72, 128, 192, 3, 64, True, 4),              # operands read as stored, every orientation
+    (264, 136, 264, 4, 8, True, 16),             # K = 136: a short last stretch of 64
+    (1032, 512, 1024, 2, 64, True, 4),           # 64 x 64 tiles in the gate/up product, wave tiles elsewhere
+]
+
+
+@pytest.mark.parametrize("case", FP32, ids=[f"t{c[0]}_h{c[1]}{'_let' if c[5] else ''}" for c in FP32])
+def test_fp32_step_matches_oracle(case):
+    """fp32 workloads: products of few tiles on wave tiles, others on 64 x 64;
+    1e-4 normwise and 1e-3 per element, as the fp32 block step's bounds."""
+    from dataclasses import replace
+    T, hidden, ffn, bits, group, let, act = case
+    w = replace(small_llama("fp32", hidden=hidden, ffn=ffn, T=T, w_bits=bits, group=group, let=let, act_bits=act),
+                bf16=False)
+    P = make_problem(w, seed=6, logit="random")
+    blk = oq.Block(T, [(s.width, s.let, s.act_bits) for s in w.sites],
+                   [(l.site, l.c_out, l.bits, l.group) for l in w.linears], dtype=torch.float32)
+    blk.ws.fill_(0xFF)
+    opt = lambda xs: [None if x is None else dev(x) for x in xs]
+    loss = blk.step(opt(P["X"]), [dev(np.ascontiguousarray(y.T)) for y in P["Y"]], opt(P["W"]),
+                    opt(P["gamma_logit"]), opt(P["beta_logit"]), s=opt(P["s"]), delta=opt(P["delta"]))
+    torch.cuda.synchronize()
+    params = {k: P[k] for k in ("W", "B", "gamma_logit", "beta_logit", "s", "delta")}
+    ref_loss, ref = block_step(w.oracle_desc(), P["X"], P["Y"], params)
+    assert abs(float(loss) - ref_loss) <= 1e-4 * abs(ref_loss)
+    names = [(blk.d_gamma, "d_gamma_logit"), (blk.d_beta, "d_beta_logit")]
+    if act < 16:
+        names += [(blk.d_s, "d_s"), (blk.d_delta, "d_delta")]
+    for got, name in names:
+        for g, r in zip(got, ref[name]):
+            if g is None:
+                continue
+            g = g.cpu().numpy().astype(np.float64)
+            assert normwise(g, r) <= 1e-4, name
+            assert np.all(np.abs(g - r) <= 1e-3 * np.maximum(np.abs(r), 1e-2 * np.abs(r).max())), name
