@@ -17,12 +17,12 @@
 // summed index gives the same sum).  K is staged in LDS row-major (XOR
 // swizzled chunks), V transposed (padded rows).
 //
-// Backward (deterministic, no atomics): one kernel per 64-key tile and key
-// head accumulates dK, dV over every query tile and query head of its group
-// (S^T, dP^T recomputed from LSE; P and dS staged per wave in LDS to become
-// A operands); a second kernel per 64-query tile accumulates dQ over the key
-// tiles, after a first sweep that forms D = sum_j P_ij dP_ij (written out for
-// the dK/dV kernel, which runs after it).
+// Backward (deterministic, no atomics): one kernel per 64-query tile forms
+// D = sum_j P_ij dP_ij in a first sweep over the key tiles (written out for
+// the other kernel, which runs after it) and accumulates dQ in a second; one
+// kernel per 64-key tile and key head accumulates dK, dV over every query tile
+// and query head of its group.  S and dP are recomputed from LSE in the
+// orientation whose accumulators are the next product's operand as they stand.
 //
 // Rounding: P and dS enter the matrix cores as bf16.  Block inputs share
 // outlier channels, so Q^, K^, V^ rows carry a large component common to all
@@ -51,6 +51,21 @@ OQ_DEV f32x4_t mfma(bf16x8_t a, bf16x8_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 OQ_DEV uint32_t pack2(float a, float b) { return f2bf2(a, b); }
+
+// The query tile (of nt per sample), head and sample of a workgroup: heads
+// vary fastest, so consecutive workgroups, which go to different XCDs, have
+// equal lengths and an XCD sees all tiles of its heads (their K and V stay in
+// its L2); the longest tiles come first.  With the tile index fastest and a
+// tile count that is a multiple of eight, XCD k would get tiles k, k + 8, ...
+// of every head: up to 1.4 times the average work (2048 tokens, 128-query
+// tiles).
+struct AttnTile {
+  int qt, h, b;
+};
+OQ_DEV AttnTile attn_tile(int H, int n_seq, int nt) {
+  const int x = int(blockIdx.x), r = x / H;
+  return {nt - 1 - r / n_seq, x % H, r % n_seq};
+}
 
 // Row-major [64][DH] bf16 tile ("K layout"), 16-byte chunk c of row r at
 // slot c ^ (r & (NCH-1)).
@@ -136,9 +151,8 @@ __global__ __launch_bounds__(ANT) void attn_fwd_kernel(const bf16raw* __restrict
   __shared__ uint4 sV[AT * DH / 8];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int fr = lane & 15, fk = lane >> 4;
-  const int ntile = S / AT;
-  const int qt = ntile - 1 - int(blockIdx.x);          // longest tiles first
-  const int h = blockIdx.y, b = blockIdx.z;
+  const AttnTile at = attn_tile(H, int(T / S), S / AT);
+  const int qt = at.qt, h = at.h, b = at.b;
   const int g = h / (H / Hkv);
   const int64_t ldq = int64_t(H) * DH, ldk = int64_t(Hkv) * DH;
   const int64_t row0 = int64_t(b) * S;
@@ -262,9 +276,8 @@ __global__ __launch_bounds__(ANT) void attn_fwd2_kernel(const bf16raw* __restric
   __shared__ uint4 sV[AT * DH / 8];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int fr = lane & 15, fk = lane >> 4;
-  const int nq = S / QW;
-  const int qt = nq - 1 - int(blockIdx.x);             // longest tiles first
-  const int h = blockIdx.y, b = blockIdx.z;
+  const AttnTile at = attn_tile(H, int(T / S), S / QW);
+  const int qt = at.qt, h = at.h, b = at.b;
   const int g = h / (H / Hkv);
   const int64_t ldq = int64_t(H) * DH, ldk = int64_t(Hkv) * DH;
   const int64_t row0 = int64_t(b) * S;
@@ -412,8 +425,8 @@ __global__ __launch_bounds__(ANT) void attn_fwd_q_kernel(const bf16raw* __restri
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int fr = lane & 15, fk = lane >> 4;
   const int ntile = S / AT;
-  const int qt = ntile - 1 - int(blockIdx.x);
-  const int h = blockIdx.y, b = blockIdx.z;
+  const AttnTile at = attn_tile(H, int(T / S), ntile);
+  const int qt = at.qt, h = at.h, b = at.b;
   const int g = h / (H / Hkv);
   const int64_t ldq = int64_t(H) * DH, ldk = int64_t(Hkv) * DH;
   const int64_t row0 = int64_t(b) * S;
@@ -546,49 +559,134 @@ __global__ __launch_bounds__(ANT) void attn_fwd_q_kernel(const bf16raw* __restri
 }
 
 // ------------------------------------------------------------------ backward
-// Operands the backward needs transposed are read from the row-major tiles
-// with ds_read_b64_tr_b16: lane i of a 16-lane group receives rows
-// k0 .. k0+3 of column c0 + i when lane j of the group points at row
-// k0 + j/4, columns c0 + 4 (j % 4) .. + 3.
-typedef short v4i16_t __attribute__((ext_vector_type(4)));
-OQ_DEV v4i16_t tr4(const void* p) {
-  typedef __attribute__((address_space(3))) v4i16_t lds_v4;
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
+// Bound by the exponentials and the vector work around the matrix
+// instructions (each about 45% of the time, partly side by side); 32-row
+// tiles with more waves per SIMD, 32 rows per wave, and 32-key workgroups were
+// no faster.  With P and dS staged through LDS, tiles double buffered in
+// registers and the tile index fastest in the grid, the backward of 32 heads
+// of 2048 tokens at 128 wide took 498 us, that of 32 heads (four per key head)
+// over four samples of 1088 at 64 wide 275; now 209 and 163, the same bits.
+// The forwards gained from the grid order alone: 87 -> 68 and 53 -> 44.
+// Tiles come from global memory straight into LDS (global_load_lds_dwordx4,
+// no registers) and are double buffered: the next tile is in flight while one
+// is used, with one barrier per tile.  16-byte chunk c of row r sits at
+// c ^ bswz(r).  Three kinds of reads share the layout: an operand's rows in
+// the order of row_of or d_row (sixteen rows, one chunk column per 16 lanes)
+// and its columns, transposed on the way (ds_read_b64_tr_b16: rows 8 f + 0..3
+// or 4..7 for two f, a 32-byte column block each).  bswz puts each on distinct
+// banks: of the rows with bit 2 alike, 0-3 and 8-11 take the eight slot pairs,
+// 16-19 and 24-27 take them again in the other order and by the other member.
+template <int DH>
+OQ_DEV int bswz(int r) {
+  const int b2 = (r >> 2) & 1, b3 = (r >> 3) & 1, b4 = (r >> 4) & 1;
+  return DH == 128 ? ((r & 3) << 1) | ((b3 ^ b4) << 3) | (b4 ^ b2)
+                   : (r & 2) | ((b3 ^ b4) << 2) | (b4 ^ b2);
 }
-OQ_DEV bf16x8_t join(v4i16_t lo, v4i16_t hi) {
+template <int DH>
+OQ_DEV bf16x8_t row_frag(const uint4* tile, int r, int c) {
+  return bits_as_bf16x8(tile[r * (DH / 8) + (c ^ bswz<DH>(r))]);
+}
+// The row of a 32-row step that row i of its accumulator tile hf stands for: a
+// lane's values (rows 4 fk + r of either tile) are then rows 8 fk + 4 hf + r,
+// an operand's k order, and feed the next product without leaving the lane.
+OQ_DEV int row_of(int hf, int i) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
+// The same within 16 rows for the sweep that forms D: blocks of four rows in
+// the order 0, 2, 3, 1 (which bswz keeps on distinct banks).
+OQ_DEV int d_row(int i) {
+  const int b0 = (i >> 2) & 1, b1 = i >> 3;
+  return 8 * (b0 ^ b1) + 4 * b1 + (i & 3);
+}
+// Lane (fk, i) gets rows 32 k2 + 8 fk + 0..7 of column 16 j + i.
+template <int DH>
+OQ_DEV bf16x8_t col_frag(const uint4* tile, int k2, int j, int lane) {
+  typedef short v4i16 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) v4i16 lds_v4;
+  const int fk = lane >> 4, jj = lane & 15;
+  const int r0 = 8 * fk + (jj >> 2), c = 2 * j + ((jj >> 1) & 1);
+  const char* t = reinterpret_cast<const char*>(tile) + 32 * k2 * (2 * DH) + 8 * (jj & 1);
+  const char* a0 = t + r0 * (2 * DH) + 16 * (c ^ bswz<DH>(r0));
+  const char* a1 = t + (r0 + 4) * (2 * DH) + 16 * (c ^ bswz<DH>(r0) ^ 1);
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(a0));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(a1));
   return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-// Operand fragment from a [64][DH] tile in the K layout: lane (fk, i) gets
-// rows kb + 8 fk + 0..7 of column cb + i (cb a multiple of 16).
+// The asynchronous copies are outside the compiler's wait counting: bwd_wait
+// stands before the barrier that publishes a tile.
+OQ_DEV void bwd_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// A value loaded before a loop, waited for here: left to itself the compiler
+// waits at the value's first use inside the loop, where the count would drain
+// the copies in flight on every pass.
+template <typename V>
+OQ_DEV void settle(V& v) {
+  asm volatile("" : "+v"(v));
+}
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+template <typename V, typename E>
+OQ_DEV V lds4(const E* p) {
+  return *reinterpret_cast<const V*>(p);
+}
+OQ_DEV bf16x8_t load_frag(const bf16raw* p) {
+  return bits_as_bf16x8(*reinterpret_cast<const uint4*>(p));
+}
+OQ_DEV uint32_t lds_byte(const void* p) {
+  return static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)(p)));
+}
+OQ_DEV void dma16(const void* base, uint32_t off, uint32_t lds) {
+  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds);
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 2\n\t"
+      "global_load_lds_dwordx4 %2, %3\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(m0v), "v"(off), "s"(base)
+      : "memory");
+}
+OQ_DEV void dma4(const void* base, uint32_t off, uint32_t lds) {
+  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds);
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 2\n\t"
+      "global_load_lds_dword %2, %3\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(m0v), "v"(off), "s"(base)
+      : "memory");
+}
+// A [64][DH] tile at g (row pitch ld): copy i of the workgroup's four waves
+// covers rows i * RS .. + RS - 1, lane offsets from tile_off.  bswz has period
+// 32; over 16 rows (RS at 128 wide) it flips the slot's bits 0 and 3.
 template <int DH>
-OQ_DEV bf16x8_t col_frag(const uint4* tile, int kb, int cb, int lane) {
+OQ_DEV uint32_t tile_off(int wave, int lane, int64_t ld) {
   constexpr int NCH = DH / 8;
-  const int fk = lane >> 4, jj = lane & 15;
-  const int cc = cb + 4 * (jj & 3);
-  const int r0 = kb + 8 * fk + (jj >> 2), r1 = r0 + 4;
-  const char* base = reinterpret_cast<const char*>(tile);
-  const char* a0 = base + r0 * (2 * DH) + 16 * ((cc >> 3) ^ (r0 & (NCH - 1))) + 2 * (cc & 7);
-  const char* a1 = base + r1 * (2 * DH) + 16 * ((cc >> 3) ^ (r1 & (NCH - 1))) + 2 * (cc & 7);
-  return join(tr4(a0), tr4(a1));
+  const int idx = 64 * wave + lane, r = idx / NCH;
+  return uint32_t(r) * uint32_t(2 * ld) + 16u * uint32_t((idx % NCH) ^ bswz<DH>(r));
 }
-// A wave's [64][16] bf16 staging tile (row pitch TS): a lane of the product's
-// C layout writes four consecutive columns of one row in one 8-byte store;
-// t16_frag gives lane (fk, i) rows kb + 8 fk + 0..7 of column i.
-constexpr int TS = 20;
-OQ_DEV void t16_put4(bf16raw* t, int row, int col, float a, float b, float c, float d) {
-  *reinterpret_cast<uint2*>(t + row * TS + col) = make_uint2(pack2(a, b), pack2(c, d));
+template <int DH>
+OQ_DEV void tile_dma(const bf16raw* g, int64_t ld, uint32_t off, uint32_t lds, int wave) {
+  constexpr int RS = ANT * 8 / DH;
+  static_assert(RS == (DH == 128 ? 16 : 32), "rows per copy");
+#pragma unroll
+  for (int i = 0; i < AT / RS; ++i)
+    dma16(g + int64_t(i * RS) * ld, DH == 128 && (i & 1) ? off ^ (16u * 9u) : off,
+          lds + uint32_t((i * 4 + wave) * 1024));
 }
-OQ_DEV bf16x8_t t16_frag(const bf16raw* t, int kb, int lane) {
-  const int fk = lane >> 4, jj = lane & 15;
-  const int r0 = kb + 8 * fk + (jj >> 2);
-  const bf16raw* a0 = t + r0 * TS + 4 * (jj & 3);
-  return join(tr4(a0), tr4(a0 + 4 * TS));
+// two fp32 values as words of two bf16 operands: hi, and the rounding's remainder lo
+OQ_DEV void split2(float a, float b, uint32_t* hi, uint32_t* lo) {
+  *hi = pack2(a, b);
+  *lo = pack2(a - __uint_as_float(*hi << 16), b - __uint_as_float(*hi & 0xffff0000u));
 }
 
-// dK, dV: one workgroup per 64-key tile and key head; each wave owns 16 keys
-// and accumulates over every query tile and query head of its group (S^T and
-// dP^T recomputed from LSE and D).  P^T and dS^T pass through the wave's
-// staging tiles, query-major, to become A operands.
+// dK, dV: one workgroup per 64 keys of a key head; each wave owns 16 keys and
+// accumulates over every query tile and query head of its group.
+// S and dP are recomputed as [queries x keys] tiles (from LSE and D) with the
+// queries in the order of row_of: two tiles of a lane's values are the B
+// operand (k = queries) of dV^T += dO^T P and dK^T += Q^T dS as they stand.
 // QP (softmax quantisation): P^ (the quantised row) enters dV, and dP goes
 // through Q_a's straight-through rule: dP = m dP^ plus the routed gradients of
 // the row's max and min (from the dQ kernel's first sweep).
@@ -596,171 +694,180 @@ template <int DH, bool QP>
 __global__ __launch_bounds__(ANT, 2) void attn_bwd_dkv_kernel(
     const bf16raw* __restrict__ Q, const bf16raw* __restrict__ K, const bf16raw* __restrict__ V,
     const bf16raw* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Dl,
-    int S, int H, int Hkv, int64_t T, float* __restrict__ dK, float* __restrict__ dV,
+    int S, int H, int Hkv, int n_seq, int64_t T, float* __restrict__ dK, float* __restrict__ dV,
     int p_bits, const float4* __restrict__ pstat, const float2* __restrict__ dmm) {
-  constexpr int KS = DH / 32, JD = DH / 16, NR = AT * DH / 8 / ANT;
-  __shared__ uint4 sQ[AT * DH / 8];
-  __shared__ uint4 sdO[AT * DH / 8];
-  __shared__ __attribute__((aligned(16))) bf16raw sP[4][AT * TS];
-  __shared__ __attribute__((aligned(16))) bf16raw sH[4][AT * TS];
-  __shared__ __attribute__((aligned(16))) bf16raw sLo[4][AT * TS];
-  __shared__ float sL[AT], sD[AT];
+  constexpr int KS = DH / 32, JD = DH / 16;
+  constexpr int QB = QP ? AT : 4;
+  constexpr int NT = AT * DH / 8;                        // 16-byte chunks of a tile
+  __shared__ uint4 sT[2][2 * NT];                       // Q, then dO
+  __shared__ __attribute__((aligned(16))) float sL[2][AT], sD[2][AT];
   // QP: per query row h, 1/h, z of Q_a, the routed max / min gradients and
   // the indices that take them
-  __shared__ float sQh[QP ? AT : 1], sQr[QP ? AT : 1], sQz[QP ? AT : 1];
-  __shared__ float sDmx[QP ? AT : 1], sDmn[QP ? AT : 1];
-  __shared__ int sAmx[QP ? AT : 1], sAmn[QP ? AT : 1];
+  __shared__ __attribute__((aligned(16))) float sQh[2][QB], sQr[2][QB], sQz[2][QB];
+  __shared__ __attribute__((aligned(16))) float sDmx[2][QB], sDmn[2][QB];
+  __shared__ __attribute__((aligned(16))) int sAmx[2][QB], sAmn[2][QB];
   const float qmax = QP ? float((1 << p_bits) - 1) : 0.0f;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int fr = lane & 15, fk = lane >> 4;
-  const int ntile = S / AT;
-  const int kt = int(blockIdx.x), g = blockIdx.y, b = blockIdx.z;
+  int rest = int(blockIdx.x);
+  const int g = rest % Hkv;
+  rest /= Hkv;
+  const int b = rest % n_seq, kt = rest / n_seq;        // longest tiles first
   const int grp = H / Hkv;
-  const int nq = ntile - kt;                           // query tiles at or after this key tile
-  const int n_it = grp * nq;
+  const int nqt = S / AT, n_it = grp * (nqt - kt);      // query tiles from the keys' own on
   const int64_t ldq = int64_t(H) * DH, ldk = int64_t(Hkv) * DH;
   const int64_t row0 = int64_t(b) * S;
   const int key_w = kt * AT + 16 * wave;                // this wave's first key
   const float sc = 1.4426950408889634f / sqrtf(float(DH));
   const float rs = 1.0f / sqrtf(float(DH));
 
+  const int64_t okv = (row0 + key_w + fr) * ldk + int64_t(g) * DH;
   bf16x8_t kf[KS], vf[KS];
-  {
-    const bf16raw* kp = K + (row0 + key_w + fr) * ldk + int64_t(g) * DH;
-    const bf16raw* vp = V + (row0 + key_w + fr) * ldk + int64_t(g) * DH;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kf[ks] = bits_as_bf16x8(*reinterpret_cast<const uint4*>(kp + 32 * ks + 8 * fk));
-      vf[ks] = bits_as_bf16x8(*reinterpret_cast<const uint4*>(vp + 32 * ks + 8 * fk));
-    }
+  for (int ks = 0; ks < KS; ++ks) {
+    kf[ks] = load_frag(K + okv + 32 * ks + 8 * fk);
+    vf[ks] = load_frag(V + okv + 32 * ks + 8 * fk);
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    settle(kf[ks]);
+    settle(vf[ks]);
   }
   f32x4_t adk[JD], adv[JD];
 #pragma unroll
   for (int j = 0; j < JD; ++j) adk[j] = adv[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // registers holding the next (query head, query tile)'s Q, dO, LSE and D
-  u32x4_t qr[NR], dr[NR];
-  float lr = 0.f, dlr = 0.f;
+  const uint32_t off = tile_off<DH>(wave, lane, ldq);
   float4 psr{};
   float2 dmr{};
-  auto fetch = [&](int it) {
-    const int hq = g * grp + it / nq, qt = kt + it % nq;
-    const int64_t qrow0 = row0 + int64_t(qt) * AT;
-    tile_to_regs<DH>(qr, Q + qrow0 * ldq + int64_t(hq) * DH, ldq, tid);
-    tile_to_regs<DH>(dr, dO + qrow0 * ldq + int64_t(hq) * DH, ldq, tid);
-    if (tid < AT) {
-      lr = LSE[int64_t(hq) * T + qrow0 + tid];
-      dlr = Dl[int64_t(hq) * T + qrow0 + tid];
-      if constexpr (QP) {
-        psr = pstat[int64_t(hq) * T + qrow0 + tid];
-        dmr = dmm[int64_t(hq) * T + qrow0 + tid];
+  // the next (query head, query tile): Q, dO, LSE and D
+  int fh = g * grp, ft = kt;
+  auto fetch = [&](int buf) {
+    const int64_t r = row0 + int64_t(ft) * AT, o = r * ldq + int64_t(fh) * DH;
+    tile_dma<DH>(Q + o, ldq, off, lds_byte(sT[buf]), wave);
+    tile_dma<DH>(dO + o, ldq, off, lds_byte(sT[buf] + NT), wave);
+    const int64_t i = int64_t(fh) * T + r;
+    if (wave == 0) dma4(LSE + i, 4u * lane, lds_byte(sL[buf]));
+    if (wave == 1) dma4(Dl + i, 4u * lane, lds_byte(sD[buf]));
+    if constexpr (QP) {
+      if (tid < AT) {
+        psr = pstat[i + tid];
+        dmr = dmm[i + tid];
       }
+    }
+    if (++ft == nqt) {
+      ft = kt;
+      ++fh;
     }
   };
   fetch(0);
-  bf16raw* tp = sP[wave];
-  bf16raw* th = sH[wave];
-  bf16raw* tl = sLo[wave];
+  int qt = kt;
   for (int it = 0; it < n_it; ++it) {
-    const int qt = kt + it % nq;
-    __syncthreads();
-    regs_to_k<DH>(sQ, qr, tid);
-    regs_to_k<DH>(sdO, dr, tid);
-    if (tid < AT) {
-      sL[tid] = lr;
-      sD[tid] = dlr;
-      if constexpr (QP) {
+    const int buf = it & 1;
+    if constexpr (QP) {
+      if (tid < AT) {
         const QParams prm = make_qparams(psr.x, psr.y, 1.0f, 1.0f, qmax);
-        sQh[tid] = prm.h;
-        sQr[tid] = prm.r;
-        sQz[tid] = prm.z;
-        sDmx[tid] = dmr.x;
-        sDmn[tid] = dmr.y;
-        sAmx[tid] = __float_as_int(psr.z);
-        sAmn[tid] = __float_as_int(psr.w);
+        sQh[buf][tid] = prm.h;
+        sQr[buf][tid] = prm.r;
+        sQz[buf][tid] = prm.z;
+        sDmx[buf][tid] = dmr.x;
+        sDmn[buf][tid] = dmr.y;
+        sAmx[buf][tid] = __float_as_int(psr.z);
+        sAmn[buf][tid] = __float_as_int(psr.w);
       }
     }
+    bwd_wait();
     __syncthreads();
-    fetch(it + 1 < n_it ? it + 1 : it);                 // in flight meanwhile
-    // S^T and dP^T [16 keys x 64 queries]: lane holds key 4 fk + r, query 16 jn + fr
-    f32x4_t st[4], dp[4];
-#pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      st[jn] = dp[jn] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        st[jn] = mfma(kf[ks], read_rm<DH>(sQ, 16 * jn + fr, 4 * ks + fk), st[jn]);
-        dp[jn] = mfma(vf[ks], read_rm<DH>(sdO, 16 * jn + fr, 4 * ks + fk), dp[jn]);
-      }
-    }
+    if (it + 1 < n_it) fetch(buf ^ 1);                   // in flight meanwhile
+    const int q0 = qt * AT;
     const bool diag = qt == kt;
-#pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      const int ql = 16 * jn + fr;
-      const float L = sL[ql], D = sD[ql];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float p = __builtin_amdgcn_exp2f(fmaf(st[jn][r], sc, -L));
-        if (diag && 16 * wave + 4 * fk + r > ql) p = 0.0f;
-        if constexpr (QP) {
-          QParams prm{};
-          prm.h = sQh[ql];
-          prm.r = sQr[ql];
-          prm.z = sQz[ql];
-          const QElem qe = quant_elem(p, prm, qmax);
-          const int key = key_w + 4 * fk + r;
-          float g = qe.m ? dp[jn][r] : 0.0f;
-          if (key == sAmx[ql]) g += sDmx[ql];
-          if (key == sAmn[ql]) g += sDmn[ql];
-          st[jn][r] = dequant(qe.q, prm);               // P^ enters dV
-          dp[jn][r] = p * (g - D) * rs;
-        } else {
-          st[jn][r] = p;
-          dp[jn][r] = p * (dp[jn][r] - D) * rs;         // dS^T (with the 1/sqrt(d) of the logits)
-        }
-      }
-      // P^T query-major: row = query, four consecutive keys
-      t16_put4(tp, ql, 4 * fk, st[jn][0], st[jn][1], st[jn][2], st[jn][3]);
-      // dS^T as two bf16 terms (hi + lo, 16 significant bits): a component
-      // shared by all queries' Q rows would otherwise meet the rounding of dS
-      float hi[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) hi[r] = bf2f(f2bf(dp[jn][r]));
-      t16_put4(th, ql, 4 * fk, hi[0], hi[1], hi[2], hi[3]);
-      t16_put4(tl, ql, 4 * fk, dp[jn][0] - hi[0], dp[jn][1] - hi[1], dp[jn][2] - hi[2],
-               dp[jn][3] - hi[3]);
-    }
-    // dV += P^T dO and dK += dS^T Q: A = rows of keys, k = queries; B = dO^T
-    // and Q^T (rows of d), read transposed from the row-major tiles
+    if (++qt == nqt) qt = kt;
+    const uint4* tq = sT[buf];
+    const uint4* to = tq + NT;
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
-      const bf16x8_t ap = t16_frag(tp, 32 * k2, lane);
-      const bf16x8_t ah = t16_frag(th, 32 * k2, lane);
-      const bf16x8_t al = t16_frag(tl, 32 * k2, lane);
+      uint32_t wp[4], wh[4], wl[4];
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        // S and dP [16 queries x 16 keys]: lane holds queries ql + r, key fr
+        const int row = 32 * k2 + row_of(hf, fr), ql = 32 * k2 + 8 * fk + 4 * hf;
+        f32x4_t st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          st = mfma(row_frag<DH>(tq, row, 4 * ks + fk), kf[ks], st);
+          dp = mfma(row_frag<DH>(to, row, 4 * ks + fk), vf[ks], dp);
+        }
+        const f32x4_t L = lds4<f32x4_t>(&sL[buf][ql]), D = lds4<f32x4_t>(&sD[buf][ql]);
+        float p[4], ds[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(st[r], sc, -L[r]));
+        f32x4_t qh, qr, qz, gmx, gmn;
+        i32x4_t imx, imn;
+        if constexpr (QP) {
+          qh = lds4<f32x4_t>(&sQh[buf][ql]);
+          qr = lds4<f32x4_t>(&sQr[buf][ql]);
+          qz = lds4<f32x4_t>(&sQz[buf][ql]);
+          gmx = lds4<f32x4_t>(&sDmx[buf][ql]);
+          gmn = lds4<f32x4_t>(&sDmn[buf][ql]);
+          imx = lds4<i32x4_t>(&sAmx[buf][ql]);
+          imn = lds4<i32x4_t>(&sAmn[buf][ql]);
+        }
+        const int key = key_w + fr;
+        if (diag) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) p[r] = key > q0 + ql + r ? 0.0f : p[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (QP) {
+            QParams prm{};
+            prm.h = qh[r];
+            prm.r = qr[r];
+            prm.z = qz[r];
+            const QElem qe = quant_elem(p[r], prm, qmax);
+            float gp = qe.m ? dp[r] : 0.0f;
+            if (key == imx[r]) gp += gmx[r];
+            if (key == imn[r]) gp += gmn[r];
+            ds[r] = p[r] * (gp - D[r]) * rs;
+            p[r] = dequant(qe.q, prm);                   // P^ enters dV
+          } else {
+            ds[r] = p[r] * (dp[r] - D[r]) * rs;  // (1/sqrt(d) of the logits)
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          wp[2 * hf + e] = pack2(p[2 * e], p[2 * e + 1]);
+          // dS as two bf16 terms (hi + lo, 16 significant bits): a component
+          // shared by all queries' Q rows would otherwise meet its rounding
+          split2(ds[2 * e], ds[2 * e + 1], &wh[2 * hf + e], &wl[2 * hf + e]);
+        }
+      }
+      const bf16x8_t bp = bits_as_bf16x8(make_uint4(wp[0], wp[1], wp[2], wp[3]));
+      const bf16x8_t bh = bits_as_bf16x8(make_uint4(wh[0], wh[1], wh[2], wh[3]));
+      const bf16x8_t bl = bits_as_bf16x8(make_uint4(wl[0], wl[1], wl[2], wl[3]));
 #pragma unroll
       for (int j = 0; j < JD; ++j) {
-        adv[j] = mfma(ap, col_frag<DH>(sdO, 32 * k2, 16 * j, lane), adv[j]);
-        const bf16x8_t bq = col_frag<DH>(sQ, 32 * k2, 16 * j, lane);
-        adk[j] = mfma(al, bq, mfma(ah, bq, adk[j]));
+        adv[j] = mfma(col_frag<DH>(to, k2, j, lane), bp, adv[j]);
+        const bf16x8_t aq = col_frag<DH>(tq, k2, j, lane);
+        adk[j] = mfma(aq, bl, mfma(aq, bh, adk[j]));
       }
     }
   }
-  // lane holds dK/dV[key_w + 4 fk + r][16 j + fr]
+  // lane holds dK/dV[key_w + fr][16 j + 4 fk + r]
 #pragma unroll
-  for (int j = 0; j < JD; ++j)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t o = (row0 + key_w + 4 * fk + r) * ldk + int64_t(g) * DH + 16 * j + fr;
-      dK[o] = adk[j][r];
-      dV[o] = adv[j][r];
-    }
+  for (int j = 0; j < JD; ++j) {
+    const f32x4_t k4 = adk[j], v4 = adv[j];
+    *reinterpret_cast<float4*>(dK + okv + 4 * fk + 16 * j) = make_float4(k4[0], k4[1], k4[2], k4[3]);
+    *reinterpret_cast<float4*>(dV + okv + 4 * fk + 16 * j) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+  }
 }
 
-// dQ: one workgroup per 64-query tile and head, four waves of 16 queries.  A
-// first sweep over the key tiles forms D = sum_j P_ij dP_ij from the very
+// dQ: one workgroup per 64 queries of a head, four waves of 16.  S^T and dP^T
+// as [keys x queries] tiles: a lane's values all belong to one query.  A first
+// sweep over the key tiles forms D = sum_j P_ij dP_ij from the very
 // probabilities the gradients use (so every row of dS sums to zero to fp32
 // rounding) and writes it for the dK/dV kernel; the second sweep accumulates
-// dQ = dS K, dS staged key-major as two bf16 terms.
+// dQ^T = K^T dS^T, dS from the lane's registers as two bf16 terms.
 // QP (softmax quantisation): the first sweep also forms Q_a's row sums
 // S_h = sum dP^ ((q - z) - m u), S_z = sum dP^ (1 - m) and E = sum P m dP^,
 // hence the row's max / min gradients (written to dmm for the dK/dV kernel)
@@ -770,196 +877,171 @@ template <int DH, bool QP>
 __global__ __launch_bounds__(ANT, 2) void attn_bwd_dq_kernel(
     const bf16raw* __restrict__ Q, const bf16raw* __restrict__ K, const bf16raw* __restrict__ V,
     const bf16raw* __restrict__ dO, const float* __restrict__ LSE, float* __restrict__ Dl,
-    int S, int H, int Hkv, int64_t T, float* __restrict__ dQ, int p_bits,
+    int S, int H, int Hkv, int n_seq, int64_t T, float* __restrict__ dQ, int p_bits,
     const float4* __restrict__ pstat, float2* __restrict__ dmm) {
-  constexpr int KS = DH / 32, JD = DH / 16, NR = AT * DH / 8 / ANT;
-  __shared__ uint4 sK[AT * DH / 8];
-  __shared__ uint4 sV[AT * DH / 8];
-  __shared__ __attribute__((aligned(16))) bf16raw sH[4][AT * TS];
-  __shared__ __attribute__((aligned(16))) bf16raw sLo[4][AT * TS];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int KS = DH / 32, JD = DH / 16;
+  constexpr int NT = AT * DH / 8;                        // 16-byte chunks of a tile
+  __shared__ uint4 sT[2][2 * NT];                       // K, then V
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int fr = lane & 15, fk = lane >> 4;
-  const int ntile = S / AT;
-  const int qt = ntile - 1 - int(blockIdx.x);
-  const int h = blockIdx.y, b = blockIdx.z;
+  const AttnTile at = attn_tile(H, n_seq, S / AT);
+  const int qt = at.qt, h = at.h, b = at.b;
   const int g = h / (H / Hkv);
   const int64_t ldq = int64_t(H) * DH, ldk = int64_t(Hkv) * DH;
   const int64_t row0 = int64_t(b) * S;
-  const int q_w = qt * AT + 16 * wave;                  // this wave's first query
+  const int q_w = qt * AT + 16 * wave, qrow = q_w + fr;   // this wave's first query, the lane's
   const float sc = 1.4426950408889634f / sqrtf(float(DH));
   const float rs = 1.0f / sqrtf(float(DH));
-
-  bf16x8_t qf[KS], df[KS];
-  {
-    const bf16raw* qp = Q + (row0 + q_w + fr) * ldq + int64_t(h) * DH;
-    const bf16raw* dp = dO + (row0 + q_w + fr) * ldq + int64_t(h) * DH;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      qf[ks] = bits_as_bf16x8(*reinterpret_cast<const uint4*>(qp + 32 * ks + 8 * fk));
-      df[ks] = bits_as_bf16x8(*reinterpret_cast<const uint4*>(dp + 32 * ks + 8 * fk));
-    }
-  }
-  // the rows this lane's accumulators hold: queries q_w + 4 fk + r
-  float lse[4], dl[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    lse[r] = LSE[int64_t(h) * T + row0 + q_w + 4 * fk + r];
-    dl[r] = 0.f;
-  }
-  // QP: per row of this wave, (1/h, z, index of the max, index of the min)
-  // and the max / min gradients once sweep 1 has them, in LDS (not registers)
-  __shared__ float4 sRq[QP ? 4 : 1][16];
-  __shared__ float2 sRg[QP ? 4 : 1][16];
   const float qmax = QP ? float((1 << p_bits) - 1) : 0.0f;
-  float sh[QP ? 4 : 1], sz[QP ? 4 : 1];
-  if constexpr (QP) {
+
+  const int64_t oq = (row0 + qrow) * ldq + int64_t(h) * DH;
+  const int64_t ri = int64_t(h) * T + row0 + qrow;
+  bf16x8_t qf[KS], df[KS];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sh[r] = sz[r] = 0.f;
-    if (lane < 16) {
-      const float4 p4 = pstat[int64_t(h) * T + row0 + q_w + lane];
-      const QParams pr = make_qparams(p4.x, p4.y, 1.0f, 1.0f, qmax);
-      sRq[wave][lane] = make_float4(pr.r, pr.z, p4.z, p4.w);
-    }
+  for (int ks = 0; ks < KS; ++ks) {
+    qf[ks] = load_frag(Q + oq + 32 * ks + 8 * fk);
+    df[ks] = load_frag(dO + oq + 32 * ks + 8 * fk);
+  }
+  float lse = LSE[ri];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    settle(qf[ks]);
+    settle(df[ks]);
+  }
+  settle(lse);
+  // QP: Q_a's parameters of the lane's row, the row's max / min and the keys
+  // that take their gradients
+  QParams pr{};
+  float gmx = 0.f, gmn = 0.f;
+  float4 p4{};
+  if constexpr (QP) {
+    p4 = pstat[ri];
+    pr = make_qparams(p4.x, p4.y, 1.0f, 1.0f, qmax);
   }
   f32x4_t adq[JD];
 #pragma unroll
   for (int j = 0; j < JD; ++j) adq[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  u32x4_t kr[NR], vr[NR];
-  const int nk = qt + 1;
-  auto fetch = [&](int t) {
-    const int64_t krow = row0 + int64_t(t) * AT;
-    tile_to_regs<DH>(kr, K + krow * ldk + int64_t(g) * DH, ldk, tid);
-    tile_to_regs<DH>(vr, V + krow * ldk + int64_t(g) * DH, ldk, tid);
+  const int nk = qt + 1;                                 // key tiles up to the diagonal
+  const uint32_t off = tile_off<DH>(wave, lane, ldk);
+  auto fetch = [&](int t, int buf) {
+    const int64_t o = (row0 + int64_t(t) * AT) * ldk + int64_t(g) * DH;
+    tile_dma<DH>(K + o, ldk, off, lds_byte(sT[buf]), wave);
+    tile_dma<DH>(V + o, ldk, off, lds_byte(sT[buf] + NT), wave);
   };
-  fetch(0);
-  bf16raw* th = sH[wave];
-  bf16raw* tl = sLo[wave];
-  for (int it = 0; it < 2 * nk; ++it) {
-    const int kt = it < nk ? it : it - nk;
-    __syncthreads();
-    regs_to_k<DH>(sK, kr, tid);
-    regs_to_k<DH>(sV, vr, tid);
-    __syncthreads();
-    fetch(kt + 1 < nk ? kt + 1 : 0);                    // in flight meanwhile
-    // S and dP [16 queries x 64 keys]: lane holds query 4 fk + r, key 16 jn + fr
-    f32x4_t st[4], dp[4];
+  // P^T and dP^T of 16 keys of the staged tile: the tile row that accumulator
+  // row fr stands for, and the key (in the sample) of this lane's first value;
+  // the lane holds keys key + r, query qrow
+  auto probs = [&](int buf, int row, int key, bool diag, float (&p)[4], f32x4_t& dp) {
+    f32x4_t st = {0.f, 0.f, 0.f, 0.f};
+    dp = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      st[jn] = dp[jn] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        st[jn] = mfma(qf[ks], read_rm<DH>(sK, 16 * jn + fr, 4 * ks + fk), st[jn]);
-        dp[jn] = mfma(df[ks], read_rm<DH>(sV, 16 * jn + fr, 4 * ks + fk), dp[jn]);
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      st = mfma(row_frag<DH>(sT[buf], row, 4 * ks + fk), qf[ks], st);
+      dp = mfma(row_frag<DH>(sT[buf] + NT, row, 4 * ks + fk), df[ks], dp);
     }
-    const bool diag = kt == qt;
 #pragma unroll
-    for (int jn = 0; jn < 4; ++jn)
+    for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(st[r], sc, -lse));
+    if (diag) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = key + r > qrow ? 0.0f : p[r];
+    }
+  };
+  fetch(0, 0);
+  // sweep 1: D (with QP, Q_a's row sums first); one sum per residue of the key
+  // index mod 16, added up as a tree over the residue's bits
+  f32x4_t dlr = {0.f, 0.f, 0.f, 0.f}, shr = dlr, szr = dlr;
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = kt & 1;
+    bwd_wait();
+    __syncthreads();
+    fetch(kt + 1 < nk ? kt + 1 : 0, buf ^ 1);             // in flight meanwhile
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float p[4];
+      f32x4_t dp;
+      probs(buf, 16 * i + d_row(fr), kt * AT + 16 * i + d_row(4 * fk), kt == qt, p, dp);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float p = __builtin_amdgcn_exp2f(fmaf(st[jn][r], sc, -lse[r]));
-        if (diag && 16 * jn + fr > 16 * wave + 4 * fk + r) p = 0.0f;
-        st[jn][r] = p;
-      }
-    if (it < nk) {
-      // sweep 1: D (with QP, Q_a's row sums first)
-#pragma unroll
-      for (int jn = 0; jn < 4; ++jn)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if constexpr (QP) {
-            const float4 rq = sRq[wave][4 * fk + r];
-            QParams pr{};
-            pr.r = rq.x;
-            pr.z = rq.y;
-            const QElem qe = quant_elem(st[jn][r], pr, qmax);
-            const float t = qe.q - pr.z;
-            sh[r] += dp[jn][r] * (qe.m ? t - qe.u : t);
-            sz[r] += qe.m ? 0.0f : dp[jn][r];
-            dl[r] += qe.m ? st[jn][r] * dp[jn][r] : 0.0f;
-          } else {
-            dl[r] += st[jn][r] * dp[jn][r];
-          }
-        }
-      if (it == nk - 1) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-#pragma unroll
-          for (int o = 1; o < 16; o <<= 1) dl[r] += __shfl_xor(dl[r], o);
-          if constexpr (QP) {
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-              sh[r] += __shfl_xor(sh[r], o);
-              sz[r] += __shfl_xor(sz[r], o);
-            }
-            const int64_t ri = int64_t(h) * T + row0 + q_w + 4 * fk + r;
-            const float4 p4 = pstat[ri];
-            const QParams pr = make_qparams(p4.x, p4.y, 1.0f, 1.0f, qmax);
-            const QGrad qg = quant_group_grad(sh[r], sz[r], p4.x, p4.y, pr, qmax);
-            dl[r] += p4.x * qg.dmx + p4.y * qg.dmn;
-            if (fr == 0) {
-              sRg[wave][4 * fk + r] = make_float2(qg.dmx, qg.dmn);
-              dmm[ri] = make_float2(qg.dmx, qg.dmn);
-            }
-          }
-        }
-        if (fr == 0) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) Dl[int64_t(h) * T + row0 + q_w + 4 * fk + r] = dl[r];
-        }
-      }
-      continue;
-    }
-    // sweep 2: dS = P (dP - D) / sqrt(d), key-major as hi + lo bf16 terms: each
-    // row of dS sums to zero, so a component shared by all K rows cancels in
-    // the exact product and must not survive the rounding of dS
-#pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      float v[4], hi[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float gp = dp[jn][r];
         if constexpr (QP) {
-          const float4 rq = sRq[wave][4 * fk + r];
-          const float2 rg = sRg[wave][4 * fk + r];
-          QParams pr{};
-          pr.r = rq.x;
-          pr.z = rq.y;
-          const QElem qe = quant_elem(st[jn][r], pr, qmax);
-          const int key = kt * AT + 16 * jn + fr;
-          gp = qe.m ? gp : 0.0f;
-          if (key == __float_as_int(rq.z)) gp += rg.x;
-          if (key == __float_as_int(rq.w)) gp += rg.y;
+          const QElem qe = quant_elem(p[r], pr, qmax);
+          const float t = qe.q - pr.z;
+          shr[r] += dp[r] * (qe.m ? t - qe.u : t);
+          szr[r] += qe.m ? 0.0f : dp[r];
+          dlr[r] += qe.m ? p[r] * dp[r] : 0.0f;
+        } else {
+          dlr[r] += p[r] * dp[r];
         }
-        v[r] = st[jn][r] * (gp - dl[r]) * rs;
-        hi[r] = bf2f(f2bf(v[r]));
-      }
-      t16_put4(th, 16 * jn + fr, 4 * fk, hi[0], hi[1], hi[2], hi[3]);
-      t16_put4(tl, 16 * jn + fr, 4 * fk, v[0] - hi[0], v[1] - hi[1], v[2] - hi[2], v[3] - hi[3]);
-    }
-    // dQ += dS K: A = dS rows (queries), k = keys; B = K^T rows (d)
-#pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
-      const bf16x8_t ah = t16_frag(th, 32 * k2, lane);
-      const bf16x8_t al = t16_frag(tl, 32 * k2, lane);
-#pragma unroll
-      for (int j = 0; j < JD; ++j) {
-        const bf16x8_t bk = col_frag<DH>(sK, 32 * k2, 16 * j, lane);
-        adq[j] = mfma(al, bk, mfma(ah, bk, adq[j]));
       }
     }
   }
+  // residue bits 0 and 1 are r; bit 2 changes with fk ^ 3, bit 3 with fk ^ 1
+  auto row_sum = [](f32x4_t v) {
+    float x = (v[0] + v[1]) + (v[2] + v[3]);
+    x += __shfl_xor(x, 48);
+    return x + __shfl_xor(x, 16);
+  };
+  float dl = row_sum(dlr);
+  if constexpr (QP) {
+    const QGrad qg = quant_group_grad(row_sum(shr), row_sum(szr), p4.x, p4.y, pr, qmax);
+    dl += p4.x * qg.dmx + p4.y * qg.dmn;
+    gmx = qg.dmx;
+    gmn = qg.dmn;
+    if (fk == 0) dmm[ri] = make_float2(gmx, gmn);
+  }
+  if (fk == 0) Dl[ri] = dl;
+  // sweep 2: dS = P (dP - D) as hi + lo bf16 terms: each row of dS sums to
+  // zero, so a component shared by all K rows cancels in the exact product and
+  // must not survive the rounding of dS
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = (nk + kt) & 1;
+    bwd_wait();
+    __syncthreads();
+    if (kt + 1 < nk) fetch(kt + 1, buf ^ 1);
 #pragma unroll
-  for (int j = 0; j < JD; ++j)
+    for (int k2 = 0; k2 < 2; ++k2) {
+      uint32_t wh[4], wl[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      dQ[(row0 + q_w + 4 * fk + r) * ldq + int64_t(h) * DH + 16 * j + fr] = adq[j][r];
+      for (int hf = 0; hf < 2; ++hf) {
+        const int key = kt * AT + 32 * k2 + 8 * fk + 4 * hf;
+        float p[4], ds[4];
+        f32x4_t dp;
+        probs(buf, 32 * k2 + row_of(hf, fr), key, kt == qt, p, dp);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float gp = dp[r];
+          if constexpr (QP) {
+            gp = quant_elem(p[r], pr, qmax).m ? gp : 0.0f;
+            if (key + r == __float_as_int(p4.z)) gp += gmx;
+            if (key + r == __float_as_int(p4.w)) gp += gmn;
+          }
+          ds[r] = p[r] * (gp - dl) * rs;
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          split2(ds[2 * e], ds[2 * e + 1], &wh[2 * hf + e], &wl[2 * hf + e]);
+      }
+      const bf16x8_t bh = bits_as_bf16x8(make_uint4(wh[0], wh[1], wh[2], wh[3]));
+      const bf16x8_t bl = bits_as_bf16x8(make_uint4(wl[0], wl[1], wl[2], wl[3]));
+      // dQ^T += K^T dS^T: A = rows of d, k = keys
+#pragma unroll
+      for (int j = 0; j < JD; ++j) {
+        const bf16x8_t ak = col_frag<DH>(sT[buf], k2, j, lane);
+        adq[j] = mfma(ak, bl, mfma(ak, bh, adq[j]));
+      }
+    }
+  }
+  // lane holds dQ[qrow][16 j + 4 fk + r]
+#pragma unroll
+  for (int j = 0; j < JD; ++j) {
+    const f32x4_t v = adq[j];
+    *reinterpret_cast<float4*>(dQ + oq + 4 * fk + 16 * j) = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
 template <int DH>
 hipError_t attn_fwd_t(const void* Q, const void* K, const void* V, int64_t T, int S, int H,
                       int Hkv, int p_bits, float* O, float* LSE, float4* pstat, hipStream_t st) {
-  const dim3 grid(unsigned(S / AT), unsigned(H), unsigned(T / S));
+  const dim3 grid(unsigned(T / AT * H));
   const auto q = static_cast<const bf16raw*>(Q);
   const auto k = static_cast<const bf16raw*>(K);
   const auto v = static_cast<const bf16raw*>(V);
@@ -967,8 +1049,7 @@ hipError_t attn_fwd_t(const void* Q, const void* K, const void* V, int64_t T, in
     hipLaunchKernelGGL(attn_fwd_q_kernel<DH>, grid, dim3(ANT), 0, st, q, k, v, S, H, Hkv, p_bits,
                        O, LSE, pstat, T);
   else if (S % (2 * AT) == 0)
-    hipLaunchKernelGGL(attn_fwd2_kernel<DH>, dim3(unsigned(S / (2 * AT)), unsigned(H), unsigned(T / S)),
-                       dim3(ANT), 0, st, q, k, v, S, H, Hkv, O, LSE, T);
+    hipLaunchKernelGGL(attn_fwd2_kernel<DH>, dim3(unsigned(T / (2 * AT) * H)), dim3(ANT), 0, st, q, k, v, S, H, Hkv, O, LSE, T);
   else
     hipLaunchKernelGGL(attn_fwd_kernel<DH>, grid, dim3(ANT), 0, st, q, k, v, S, H, Hkv, O, LSE, T);
   return hipGetLastError();
@@ -983,13 +1064,13 @@ void attn_bwd_launch(const void* Q, const void* K, const void* V, const void* dO
   const auto k = static_cast<const bf16raw*>(K);
   const auto v = static_cast<const bf16raw*>(V);
   const auto o = static_cast<const bf16raw*>(dO);
+  const int n_seq = int(T / S);
   // dQ first: it also writes D (and, quantised, the max / min gradients),
   // which the dK/dV kernel reads
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, QP>), dim3(unsigned(S / AT), unsigned(H), unsigned(T / S)),
-                     dim3(ANT), 0, st, q, k, v, o, LSE, Dl, S, H, Hkv, T, dQ, p_bits, pstat, dmm);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<DH, QP>), dim3(unsigned(S / AT), unsigned(Hkv), unsigned(T / S)),
-                     dim3(ANT), 0, st, q, k, v, o, LSE, Dl, S, H, Hkv, T, dK, dV, p_bits, pstat,
-                     dmm);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, QP>), dim3(unsigned(T / AT * H)), dim3(ANT), 0, st,
+                     q, k, v, o, LSE, Dl, S, H, Hkv, n_seq, T, dQ, p_bits, pstat, dmm);
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<DH, QP>), dim3(unsigned(T / AT * Hkv)), dim3(ANT), 0,
+                     st, q, k, v, o, LSE, Dl, S, H, Hkv, n_seq, T, dK, dV, p_bits, pstat, dmm);
 }
 
 template <int DH>
