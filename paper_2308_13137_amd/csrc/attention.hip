@@ -625,6 +625,11 @@ template <typename V, typename E>
 OQ_DEV V lds4(const E* p) {
   return *reinterpret_cast<const V*>(p);
 }
+// four fp32 gradients at any float's address
+OQ_DEV void store4(float* p, f32x4_t v) {
+  typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+  *reinterpret_cast<f32x4u_t*>(p) = v;
+}
 OQ_DEV bf16x8_t load_frag(const bf16raw* p) {
   return bits_as_bf16x8(*reinterpret_cast<const uint4*>(p));
 }
@@ -856,9 +861,8 @@ __global__ __launch_bounds__(ANT, 2) void attn_bwd_dkv_kernel(
   // lane holds dK/dV[key_w + fr][16 j + 4 fk + r]
 #pragma unroll
   for (int j = 0; j < JD; ++j) {
-    const f32x4_t k4 = adk[j], v4 = adv[j];
-    *reinterpret_cast<float4*>(dK + okv + 4 * fk + 16 * j) = make_float4(k4[0], k4[1], k4[2], k4[3]);
-    *reinterpret_cast<float4*>(dV + okv + 4 * fk + 16 * j) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+    store4(dK + okv + 4 * fk + 16 * j, adk[j]);
+    store4(dV + okv + 4 * fk + 16 * j, adv[j]);
   }
 }
 
@@ -1032,10 +1036,7 @@ __global__ __launch_bounds__(ANT, 2) void attn_bwd_dq_kernel(
   }
   // lane holds dQ[qrow][16 j + 4 fk + r]
 #pragma unroll
-  for (int j = 0; j < JD; ++j) {
-    const f32x4_t v = adq[j];
-    *reinterpret_cast<float4*>(dQ + oq + 4 * fk + 16 * j) = make_float4(v[0], v[1], v[2], v[3]);
-  }
+  for (int j = 0; j < JD; ++j) store4(dQ + oq + 4 * fk + 16 * j, adq[j]);
 }
 
 template <int DH>
