@@ -168,30 +168,10 @@ __global__ __launch_bounds__(256) void colstat_kernel(const TX* __restrict__ X, 
   }
 }
 
-// Column sums of [rows, C] partial arrays: a block of 16 waves covers 64
-// columns (lane = column); wave w adds rows w, w + 16, ... in fp64 into four
-// accumulators (four loads in flight; row w + 16 k goes to accumulator
-// k % 4), and the 16 wave sums are combined through LDS in wave order.  Every
-// order is fixed, so the result is deterministic.
+// Column sums of [rows, C] partial arrays: class w of 16 adds rows w, w + 16,
+// ... of a column in fp64 and the 16 class sums are combined through LDS in
+// order.  Every order is fixed, so the result is deterministic.
 constexpr int CS_WAVES = 16;
-
-OQ_DEV double strip_sum(const float* parts, int64_t rows, int64_t C, int64_t c, int w) {
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (parts && c < C) {
-    int64_t i = w;
-    for (; i + 3 * CS_WAVES < rows; i += 4 * CS_WAVES) {
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = parts[(i + u * CS_WAVES) * C + c];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] += double(v[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-      if (i + u * CS_WAVES < rows) acc[u] += double(parts[(i + u * CS_WAVES) * C + c]);
-  }
-  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-}
 
 template <int NA>
 OQ_DEV void strip_combine(double (&v)[NA], double (*sh)[CS_WAVES][64], int w, int lane) {
@@ -206,19 +186,52 @@ OQ_DEV void strip_combine(double (&v)[NA], double (*sh)[CS_WAVES][64], int w, in
   }
 }
 
-__global__ __launch_bounds__(64 * CS_WAVES) void let_grad_finish_kernel(
+// The two LET gradients: y = 0 d_s from pw and psx, y = 1 d_delta from pb and
+// ps1.  32 columns by 16 classes per block (row w + 16 k goes to accumulator
+// k % 4 of class w): a wave reads two rows' 128-byte lines, sixteen rows in
+// flight per thread.  Bound by the
+// partials' reads (81 MB for the q, k, v site of a 4096-wide block); with 64
+// columns by 16 waves, four loads in flight and all four sums in one block
+// only a quarter of the compute units worked: 32 -> 19 us, the same bits.
+constexpr int LG_COLS = 32;
+
+OQ_DEV double class_sum(const float* parts, int64_t rows, int64_t C, int64_t c, int w) {
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  if (!parts) return 0.0;
+  constexpr int U = 16;
+  int64_t i = w;
+  for (; i + (U - 1) * CS_WAVES < rows; i += U * CS_WAVES) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = parts[(i + u * CS_WAVES) * C + c];
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc[u % 4] += double(v[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < U - 1; ++u)
+    if (i + u * CS_WAVES < rows) acc[u % 4] += double(parts[(i + u * CS_WAVES) * C + c]);
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+__global__ __launch_bounds__(LG_COLS* CS_WAVES) void let_grad_finish_kernel(
     int64_t C, const float* s, const float* pw, int64_t npw, const float* psx, const float* ps1,
     int64_t npa, const float* pb, int64_t npb, float* d_s, float* d_delta) {
-  __shared__ double sh[4][CS_WAVES][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t c = int64_t(blockIdx.x) * 64 + lane;
-  double v[4] = {strip_sum(pw, npw, C, c, w), strip_sum(psx, npa, C, c, w),
-                 strip_sum(ps1, npa, C, c, w), strip_sum(pb, npb, C, c, w)};
-  strip_combine<4>(v, sh, w, lane);
+  __shared__ double sh[2][CS_WAVES][LG_COLS];
+  const int col = threadIdx.x % LG_COLS, w = threadIdx.x / LG_COLS;
+  const int64_t c = int64_t(blockIdx.x) * LG_COLS + col;
+  const bool first = blockIdx.y == 0;
+  float* out = first ? d_s : d_delta;
+  if (!out) return;
+  if (c < C) {
+    sh[0][w][col] = first ? class_sum(pw, npw, C, c, w) : class_sum(pb, npb, C, c, w);
+    sh[1][w][col] = class_sum(first ? psx : ps1, npa, C, c, w);
+  }
+  __syncthreads();
   if (w != 0 || c >= C) return;
-  const double sc = s ? double(s[c]) : 1.0;
-  if (d_s) d_s[c] = float(v[0] - v[1] / sc);
-  if (d_delta) d_delta[c] = float(v[3] - v[2] / sc);
+  double v = 0.0, x = 0.0;
+  for (int k = 0; k < CS_WAVES; ++k) v += sh[0][k][col];
+  for (int k = 0; k < CS_WAVES; ++k) x += sh[1][k][col];
+  out[c] = float(v - x / (s ? double(s[c]) : 1.0));
 }
 
 __global__ __launch_bounds__(64 * CS_WAVES) void let_init_finish_kernel(
@@ -498,8 +511,8 @@ hipError_t let_grad_finish(int64_t C, const float* s, const float* pw, int64_t n
                            const float* psx, const float* ps1, int64_t npa, const float* pb,
                            int64_t npb, float* d_s, float* d_delta, hipStream_t st) {
   if (C <= 0) return hipSuccess;
-  hipLaunchKernelGGL(let_grad_finish_kernel, dim3(unsigned((C + 63) / 64)), dim3(64 * CS_WAVES), 0, st, C,
-                     s, pw, npw, psx, ps1, npa, pb, npb, d_s, d_delta);
+  hipLaunchKernelGGL(let_grad_finish_kernel, dim3(unsigned((C + LG_COLS - 1) / LG_COLS), 2),
+                     dim3(LG_COLS * CS_WAVES), 0, st, C, s, pw, npw, psx, ps1, npa, pb, npb, d_s, d_delta);
   return hipGetLastError();
 }
 
