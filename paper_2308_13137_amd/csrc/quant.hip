@@ -272,7 +272,7 @@ __global__ __launch_bounds__(NT) void lwc_fwd_kernel(
 // per element: dW~ = g*m + [i = argmax] dmax + [i = argmin] dmin
 // per column (optional): partial sum over this block's rows of dW~ * W.
 template <typename TW, int KC, bool WHOLE_ROW, bool LETW, int NTB = NT>
-__global__ __launch_bounds__(NTB) void lwc_bwd_kernel(
+__global__ __launch_bounds__(NTB, WHOLE_ROW && !LETW && NTB == 512 && KC == 3 ? 4 : 1) void lwc_bwd_kernel(
     const TW* __restrict__ W, int64_t c_out, int64_t c_in, const float* __restrict__ s,
     const float* __restrict__ gl, const float* __restrict__ bl, int bits, int group, int R,
     const float* __restrict__ dW, float* __restrict__ dgl, float* __restrict__ dbl,
@@ -371,13 +371,18 @@ __global__ __launch_bounds__(NTB) void lwc_bwd_kernel(
       }
       const QParams p = make_group_qparams(quant, st.mx, st.mn, gl[row], bl[row], qmax);
       float2 sums = make_float2(0.f, 0.f);
+      uint32_t inside[KC];                               // the elements' clip flags
 #pragma unroll
       for (int k = 0; k < KC; ++k) {
         const int j = tid + NTB * k;
+        inside[k] = 0u;
         if (j < cpr) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            group_terms(quant, g[k][e], quant_elem(wt_at(k, e), p, qmax), p, qmax, sums.x, sums.y);
+          for (int e = 0; e < 8; ++e) {
+            const QElem qe = quant_elem(wt_at(k, e), p, qmax);
+            inside[k] |= qe.m ? 1u << e : 0u;
+            group_terms(quant, g[k][e], qe, p, qmax, sums.x, sums.y);
+          }
         }
       }
       sums.x = wave_sum(sums.x);
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(NTB) void lwc_bwd_kernel(
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const int col = 8 * j + e;
-              float x = quant_elem(wt_at(k, e), p, qmax).m ? gg[e] : 0.0f;
+              float x = (inside[k] >> e) & 1u ? gg[e] : 0.0f;
               if (quant == WQ_LWC) {
                 if (col == st.imx) x += qg.dmx;
                 if (col == st.imn) x += qg.dmn;
@@ -1012,7 +1017,7 @@ __global__ __launch_bounds__(NT) void lwc_fwd_row_kernel(
 
 // ------------------------------------------------------------------ activation forward
 // x~ = (x - delta) * (1/s); per token row Eq. 2 with gamma = beta = 1.
-template <typename TX, typename TQ, int KC, int NTB = NT>
+template <typename TX, typename TQ, int KC, int NTB, bool LET>
 __global__ __launch_bounds__(NTB) void act_fwd_kernel(
     const TX* __restrict__ X, int64_t T, int64_t C, int bits, const float* __restrict__ s,
     const float* __restrict__ delta, int R, TQ* __restrict__ xdq, uint8_t* __restrict__ codes,
@@ -1023,9 +1028,10 @@ __global__ __launch_bounds__(NTB) void act_fwd_kernel(
   const bool quant = bits < 16;
   const float qmax = quant ? float((1 << bits) - 1) : 0.0f;
   const float qs = quant ? float((1 << (bits - 1)) - 1) : 0.0f;
-  float rs[KC][8], dl[KC][8];
+  constexpr int KL = LET ? KC : 1;
+  float rs[KL][8], dl[KL][8];
 #pragma unroll
-  for (int k = 0; k < KC; ++k) {
+  for (int k = 0; k < (LET ? KC : 0); ++k) {
     const int j = tid + NTB * k;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -1041,7 +1047,6 @@ __global__ __launch_bounds__(NTB) void act_fwd_kernel(
       if (delta) load8(delta + 8 * j, dl[k]);
     }
   }
-  const bool let = s || delta;
   const int64_t r0 = int64_t(blockIdx.x) * R;
   const int64_t r1 = min(T, r0 + R);
   for (int64_t row = r0; row < r1; ++row) {
@@ -1054,7 +1059,7 @@ __global__ __launch_bounds__(NTB) void act_fwd_kernel(
         load8(X + row * C + 8 * j, v[k]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          if (let) v[k][e] = (v[k][e] - dl[k][e]) * rs[k][e];
+          if constexpr (LET) v[k][e] = (v[k][e] - dl[k][e]) * rs[k][e];
           minmax_add(st, v[k][e], 8 * j + e);
         }
       }
@@ -1093,14 +1098,32 @@ __global__ __launch_bounds__(NTB) void act_fwd_kernel(
   }
 }
 
+// Without quantisation and LET the activations only change type, eight
+// elements per thread (2,048 x 28,672 fp32 to bf16: 199 -> 55 us).
+template <typename TX, typename TQ>
+__global__ __launch_bounds__(NT) void act_convert_kernel(const TX* __restrict__ X, int64_t n8,
+                                                         TQ* __restrict__ xdq) {
+  for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < n8; i += int64_t(gridDim.x) * NT) {
+    float v[8];
+    load8(X + 8 * i, v);
+    store8(xdq + 8 * i, v);
+  }
+}
+
 // ------------------------------------------------------------------ activation backward
 // dx~ per element (straight-through with the row scale's gradient); per column
 // partial sums over this block's rows of dx~ * x~ and of dx~.
 // One barrier per block reduction (lds_barrier): the LDS slots of the two
 // reductions alternate, and a wave reads each slot before it arrives at the
 // other reduction's barrier, so no second barrier guards the rewrite.
-template <typename TX, int KC, int NTB = NT>
-__global__ __launch_bounds__(NTB) void act_bwd_kernel(
+// LET (s, delta or the partials are given): four more arrays per thread, rows
+// of a block in sequence.  At 4,096 channels three blocks of it fit a compute
+// unit only below 171 VGPRs: its 683 blocks of 2,048 tokens then run as one
+// round, not two (launch bounds 3: 40 -> 33 us).  Without LET rows are
+// independent: one block per row (2,048 x 4,096: 40 -> 26 us; x 11,008: 115 ->
+// 66 us).
+template <typename TX, int KC, int NTB, bool LET>
+__global__ __launch_bounds__(NTB, LET && KC == 2 && NTB == 256 ? 3 : 1) void act_bwd_kernel(
     const TX* __restrict__ X, int64_t T, int64_t C, int bits, const float* __restrict__ s,
     const float* __restrict__ delta, int R, const float* __restrict__ dXdq,
     float* __restrict__ dXt, float* __restrict__ p_sx, float* __restrict__ p_s1, bool sym) {
@@ -1112,9 +1135,10 @@ __global__ __launch_bounds__(NTB) void act_bwd_kernel(
   const bool quant = bits < 16;
   const float qmax = quant ? float((1 << bits) - 1) : 0.0f;
   const float qs = quant ? float((1 << (bits - 1)) - 1) : 0.0f;
-  float rs[KC][8], dl[KC][8], asx[KC][8], as1[KC][8];
+  constexpr int KL = LET ? KC : 1;
+  float rs[KL][8], dl[KL][8], asx[KL][8], as1[KL][8];
 #pragma unroll
-  for (int k = 0; k < KC; ++k) {
+  for (int k = 0; k < (LET ? KC : 0); ++k) {
     const int j = tid + NTB * k;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -1132,12 +1156,12 @@ __global__ __launch_bounds__(NTB) void act_bwd_kernel(
       if (delta) load8(delta + 8 * j, dl[k]);
     }
   }
-  const bool let = s || delta;
   const int64_t r0 = int64_t(blockIdx.x) * R;
   const int64_t r1 = min(T, r0 + R);
-  // up to two chunks per thread, the next row's X and dX^ are loaded while
-  // this row is reduced (wider rows would spill)
-  constexpr bool PF = KC <= 2;
+  // with LET and up to two chunks per thread, the next row's X and dX^ are
+  // loaded while this row is reduced (wider rows would spill; without LET a
+  // block has one row)
+  constexpr bool PF = LET && KC <= 2;
   Chunk8<TX> xn[KC];
   float gn[KC][8];
   auto issue = [&](int64_t row) {
@@ -1182,7 +1206,7 @@ __global__ __launch_bounds__(NTB) void act_bwd_kernel(
       if (j < cpr) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          if (let) v[k][e] = (v[k][e] - dl[k][e]) * rs[k][e];
+          if constexpr (LET) v[k][e] = (v[k][e] - dl[k][e]) * rs[k][e];
           minmax_add(st, v[k][e], 8 * j + e);
         }
       }
@@ -1257,15 +1281,17 @@ __global__ __launch_bounds__(NTB) void act_bwd_kernel(
       if (j < cpr) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          asx[k][e] += g[k][e] * v[k][e];
-          as1[k][e] += g[k][e];
+          if constexpr (LET) {
+            asx[k][e] += g[k][e] * v[k][e];
+            as1[k][e] += g[k][e];
+          }
         }
         if (dXt) store8(dXt + row * C + 8 * j, g[k]);
       }
     }
   }
 #pragma unroll
-  for (int k = 0; k < KC; ++k) {
+  for (int k = 0; k < (LET ? KC : 0); ++k) {
     const int j = tid + NTB * k;
     if (j < cpr) {
       if (p_sx) store8(p_sx + int64_t(blockIdx.x) * C + 8 * j, asx[k]);
@@ -1354,6 +1380,7 @@ int rows_per_block(int64_t rows, int64_t target_blocks) {
 
 constexpr int64_t LWC_BLOCKS = 768;
 constexpr int64_t ACT_BLOCKS = 768;
+constexpr int64_t ROW_BLOCKS = 1 << 20;  // one block per row up to here
 
 #define OQ_KC_SWITCH(KCV, ...)                      \
   switch (KCV) {                                    \
@@ -1627,13 +1654,23 @@ hipError_t lwc_bwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
                          dim3(NTc), 0, st, static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits,
                          int(group), R, dW, dgl, dbl, dW_tilde, ds_parts, quant, gs);
     } else {
-      // no partials: one round of resident blocks
-      const int R = rows_per_block(
-          c_out, resident_blocks(reinterpret_cast<const void*>(lwc_bwd_kernel<TW, KCc, WR, false, NTc>),
-                                 0, NTc));
-      hipLaunchKernelGGL((lwc_bwd_kernel<TW, KCc, WR, false, NTc>), dim3(unsigned((c_out + R - 1) / R)),
-                         dim3(NTc), 0, st, static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits,
-                         int(group), R, dW, dgl, dbl, dW_tilde, ds_parts, quant, gs);
+      // no partials: one round of resident blocks; whole rows of up to three
+      // quarters of a width take that many chunks, for two blocks per compute
+      // unit (4,096 rows of 11,008: 125 -> 90 us)
+      auto plain = [&](auto kcp) {
+        constexpr int K = decltype(kcp)::value;
+        const auto kernel = lwc_bwd_kernel<TW, K, WR, false, NTc>;
+        const int R = rows_per_block(
+            c_out, resident_blocks(reinterpret_cast<const void*>(kernel), 0, NTc));
+        hipLaunchKernelGGL(kernel, dim3(unsigned((c_out + R - 1) / R)), dim3(NTc), 0, st,
+                           static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits, int(group), R,
+                           dW, dgl, dbl, dW_tilde, ds_parts, quant, gs);
+      };
+      constexpr int K34 = WR && KCc >= 4 ? KCc / 4 * 3 : KCc;
+      if (c_in / 8 <= K34 * NTc)
+        plain(std::integral_constant<int, K34>{});
+      else
+        plain(std::integral_constant<int, KCc>{});
     }
   };
   auto by_kc = [&](auto tw, auto wr) -> hipError_t {
@@ -1685,22 +1722,42 @@ hipError_t act_fwd(const void* X, bool x_bf16, int64_t T, int64_t C, int bits, c
     else by_ch(float{});
     return hipGetLastError();
   }
-  const int R = rows_per_block(T, ACT_BLOCKS);
+  const bool let = s || delta;
+  if (bits >= 16 && !let && X_dq && x_bf16 != dq_bf16) {
+    const int64_t n8 = T * C / 8;
+    const dim3 g8(unsigned(std::min<int64_t>((n8 + NT - 1) / NT, 1 << 20)));
+    if (x_bf16)
+      hipLaunchKernelGGL((act_convert_kernel<uint16_t, float>), g8, dim3(NT), 0, st,
+                         static_cast<const uint16_t*>(X), n8, static_cast<float*>(X_dq));
+    else
+      hipLaunchKernelGGL((act_convert_kernel<float, uint16_t>), g8, dim3(NT), 0, st,
+                         static_cast<const float*>(X), n8, static_cast<uint16_t*>(X_dq));
+    return hipGetLastError();
+  }
+  // without LET there is nothing to keep across rows: one block per row, few
+  // registers (2,048 x 11,008 fp32: 67 -> 39 us; x 4,096: 17 -> 14 us)
+  const int R = let ? rows_per_block(T, ACT_BLOCKS) : rows_per_block(T, ROW_BLOCKS);
   const dim3 grid(unsigned((T + R - 1) / R));
-  auto go = [&](auto tx, auto tq, auto kcc) {
+  auto launch = [&](auto tx, auto tq, auto kcc, auto nt, auto lt) {
     using TX = decltype(tx);
     using TQ = decltype(tq);
-    constexpr int KCc = decltype(kcc)::value;
-    if constexpr (KCc >= 8) {
-      // wide rows: twice the threads per row, half the chunks per thread
-      hipLaunchKernelGGL((act_fwd_kernel<TX, TQ, KCc / 2, 2 * NT>), grid, dim3(2 * NT), 0, st,
-                         static_cast<const TX*>(X), T, C, bits, s, delta, R, static_cast<TQ*>(X_dq),
-                         codes, h, z, sym);
-    } else {
-      hipLaunchKernelGGL((act_fwd_kernel<TX, TQ, KCc>), grid, dim3(NT), 0, st,
-                         static_cast<const TX*>(X), T, C, bits, s, delta, R, static_cast<TQ*>(X_dq),
-                         codes, h, z, sym);
-    }
+    constexpr int NTc = decltype(nt)::value;
+    hipLaunchKernelGGL((act_fwd_kernel<TX, TQ, decltype(kcc)::value, NTc, decltype(lt)::value>),
+                       grid, dim3(NTc), 0, st, static_cast<const TX*>(X), T, C, bits, s, delta, R,
+                       static_cast<TQ*>(X_dq), codes, h, z, sym);
+  };
+  // wide rows: twice the threads per row, half the chunks per thread
+  auto go = [&](auto tx, auto tq, auto kcc) {
+    constexpr int KC0 = decltype(kcc)::value;
+    constexpr int NTc = KC0 >= 8 ? 2 * NT : NT, KCc = KC0 >= 8 ? KC0 / 2 : KC0;
+    constexpr int K34 = KCc >= 4 ? KCc / 4 * 3 : KCc;
+    const std::integral_constant<int, NTc> nt{};
+    if (let)
+      launch(tx, tq, std::integral_constant<int, KCc>{}, nt, std::true_type{});
+    else if (C / 8 <= K34 * NTc)
+      launch(tx, tq, std::integral_constant<int, K34>{}, nt, std::false_type{});
+    else
+      launch(tx, tq, std::integral_constant<int, KCc>{}, nt, std::false_type{});
   };
   auto by_kc = [&](auto tx, auto tq) -> hipError_t {
     OQ_KC_SWITCH(kc, go(tx, tq, std::integral_constant<int, KC>{}))
@@ -1725,22 +1782,32 @@ hipError_t act_bwd(const void* X, bool x_bf16, int64_t T, int64_t C, int bits, c
   const int kc = kc_for(C);
   if (C <= 0 || C % 8 || kc == 0) return hipErrorInvalidValue;
   if (T <= 0) return hipSuccess;
-  const int R = rows_per_block(T, ACT_BLOCKS);
+  const bool let = s || delta || p_sx || p_s1;
+  // (one block per row as long as the grid's threads stay below 2^32)
+  const int R = let ? rows_per_block(T, ACT_BLOCKS) : rows_per_block(T, ROW_BLOCKS);
   const dim3 grid(unsigned((T + R - 1) / R));
-  auto go = [&](auto tx, auto kcc) {
+  auto launch = [&](auto tx, auto kcc, auto nt, auto lt) {
     using TX = decltype(tx);
-    constexpr int KCc = decltype(kcc)::value;
-    if constexpr (KCc >= 8) {
-      // wide rows: twice the threads per row, half the chunks per thread
-      // (256 threads with 8 chunks each leave one wave per SIMD)
-      hipLaunchKernelGGL((act_bwd_kernel<TX, KCc / 2, 2 * NT>), grid, dim3(2 * NT), 0, st,
-                         static_cast<const TX*>(X), T, C, bits, s, delta, R, dXdq, dXt, p_sx, p_s1,
-                         sym && bits < 16);
-    } else {
-      hipLaunchKernelGGL((act_bwd_kernel<TX, KCc>), grid, dim3(NT), 0, st,
-                         static_cast<const TX*>(X), T, C, bits, s, delta, R, dXdq, dXt, p_sx, p_s1,
-                         sym && bits < 16);
-    }
+    constexpr int NTc = decltype(nt)::value;
+    hipLaunchKernelGGL((act_bwd_kernel<TX, decltype(kcc)::value, NTc, decltype(lt)::value>), grid,
+                       dim3(NTc), 0, st, static_cast<const TX*>(X), T, C, bits, s, delta, R, dXdq,
+                       dXt, p_sx, p_s1, sym && bits < 16);
+  };
+  // wide rows (more than 4 chunks per thread): twice the threads per row, half
+  // the chunks per thread (256 threads with 8 chunks each leave one wave per
+  // SIMD); without LET rows of up to three quarters of a width take that many
+  // chunks (fewer registers; the order of the sums is the threads', unchanged)
+  auto go = [&](auto tx, auto kcc) {
+    constexpr int KC0 = decltype(kcc)::value;
+    constexpr int NTc = KC0 >= 8 ? 2 * NT : NT, KCc = KC0 >= 8 ? KC0 / 2 : KC0;
+    constexpr int K34 = KCc >= 4 ? KCc / 4 * 3 : KCc;
+    const std::integral_constant<int, NTc> nt{};
+    if (let)
+      launch(tx, std::integral_constant<int, KCc>{}, nt, std::true_type{});
+    else if (C / 8 <= K34 * NTc)
+      launch(tx, std::integral_constant<int, K34>{}, nt, std::false_type{});
+    else
+      launch(tx, std::integral_constant<int, KCc>{}, nt, std::false_type{});
   };
   auto by_kc = [&](auto tx) -> hipError_t {
     OQ_KC_SWITCH(kc, go(tx, std::integral_constant<int, KC>{}))
