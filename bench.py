@@ -36,16 +36,17 @@ GEMM_SOURCES = ("paper_2308_13137_amd/csrc/gemm.hip", "paper_2308_13137_amd/csrc
 COPY_BYTES = 1 << 30          # calibration copy: 1 GiB read, 1 GiB written
 
 
-# sources whose text defines the packed linear's kernel
+# sources whose text defines the packed linear's kernels
 PACKED_SOURCES = ("paper_2308_13137_amd/csrc/packed.hip", "paper_2308_13137_amd/csrc/packed.h",
-                  "paper_2308_13137_amd/csrc/common.h")
+                  "paper_2308_13137_amd/csrc/packed_linear.h", "paper_2308_13137_amd/csrc/common.h")
+PACKED_KERNELS = ("packed_linear_kernel", "packed_mfma_kernel", "packed_tile_kernel")
 # per dominant kernel: its sources, the key of their hash in the summary, the
 # dispatches the counters are read from, and what they are called
 TRAFFIC_KINDS = {
     "gemm_fwd": (GEMM_SOURCES, "gemm source hash",
                  lambda n: "gemm_bf16_w8_kernel" in n and "EpiResid" in n, "the forward product"),
-    "packed_linear": (PACKED_SOURCES, "packed source hash", lambda n: "packed_linear_kernel" in n,
-                      "the packed-weight linear"),
+    "packed_linear": (PACKED_SOURCES, "packed source hash",
+                      lambda n: any(k in n for k in PACKED_KERNELS), "the packed-weight linear"),
 }
 
 

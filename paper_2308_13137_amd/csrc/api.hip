@@ -1079,7 +1079,7 @@ oq_status oq_block_calib_step(const oq_block_desc* d, const void* const* Y_fp_T,
     }
     // the zeros that round the gradient products' K up to whole stages: dY^T's
     // columns T .. Tp and, for the input gradient, its and W^'s rows M .. Mp
-    // (2000 tokens against 2048, 7B W4A4 LET block: 3.96 -> 3.2 ms; the step
+    // (2000 tokens against 2048, 7B W4A4 LET block: 3.90 -> 3.06 ms; the step
     // transposed X^, dY and W^ before)
     if (direct && (Tp != T || Mp != M)) {
       ProfScope ps(PK_OTHER, st, double(M) * (Tp - T) * 2);
