@@ -478,6 +478,9 @@ template <int N>
 OQ_DEV void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
 }
+// until the wave's LDS reads have their data: before a copy into a slot that they
+// read (the compiler would let a read's value arrive after the copy is issued)
+OQ_DEV void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 OQ_DEV uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) const char*)(p)));
@@ -849,8 +852,12 @@ __global__ __launch_bounds__(PM_THREADS) void packed_mfma_kernel(
         for (int ub = 0; ub < UB; ++ub)
           if (KEEP || b0 + ub < nblk)           // KEEP: a missing block's activations are zeros
             compute(b0 + ub, ub, slot, KEEP ? keep + size_t(2 * k + ub) * n_tok * 256 : slot + Cfg::WB + Cfg::HZ * 4, 256);
-        if (left > 0) prefetch(s);
-        else --inflight;
+        if (left > 0) {
+          wait_lds_reads();
+          prefetch(s);
+        } else {
+          --inflight;
+        }
         s = s + 1 == D ? 0 : s + 1;
       }
     finish(tile, n);
