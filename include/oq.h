@@ -481,9 +481,10 @@ oq_status oq_pack_codes(const uint8_t* codes, int64_t c_out, int64_t c_in, int b
  * tokens with groups that are no multiple of 128: the vector kernel); more
  * tokens take a tiled kernel.  n_tok == 0 or c_out == 0 is a no-op that accepts
  * NULL pointers.  Products of codes and activations are exact in fp32 and the
- * sums run in a fixed order, so results are reproducible; within one of the
- * three kernels a token's outputs do not depend on the other tokens of its
- * batch.
+ * sums run in a fixed order, so results are reproducible.  With groups that are
+ * a multiple of 128 a token's outputs do not depend on the other tokens of its
+ * batch, whatever its size; with other groups they do not among batches of 1 or
+ * 2, of 3 to 96 and of more than 96 tokens.
  */
 oq_status oq_packed_linear(const void* X, oq_dtype x_dt, int64_t n_tok, int64_t c_in,
                            const uint8_t* packed, int bits, int64_t group, const float* h,

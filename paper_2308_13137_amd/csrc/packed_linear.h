@@ -14,7 +14,7 @@
 // kernel at up to 7 tokens and the former matrix-core kernel above):
 //   W4, 1 token 38.4 -> 37.1 us; W3, 1 token 44.9 -> 38.1; W4, 4 tokens 66 -> 43;
 //   8 tokens 51 -> 47; 16 tokens 57 -> 49; W3, 24 tokens 80 -> 63; W2 g64 (13B),
-//   4 tokens 103 -> 66; W4, 500 tokens 1274 -> 445.
+//   4 tokens 103 -> 66; W4, 500 tokens 1274 -> 460.
 // Against 64-bit sums the results are 4 to 40 times closer than before (the codes'
 // offset is 2^BITS instead of 128, so less cancels).
 #pragma once
@@ -511,7 +511,8 @@ OQ_DEV uint32_t lds_addr(const void* p) {
 // activations is copied once.  In LDS chunk c of row r sits at c ^ swz(r), so
 // the lanes of one operand read hit distinct banks.
 //
-// The waves' partial outputs are added in wave order through LDS; a token's
+// The waves' partial outputs are added through LDS, the even waves' and the odd
+// waves' in order and then the two sums, as the tiled kernel adds them; a token's
 // sums depend neither on the other tokens of its batch nor on RT.
 constexpr int PM_THREADS = 512;
 constexpr int PM_WAVES = PM_THREADS / 64;
@@ -759,9 +760,10 @@ __global__ __launch_bounds__(PM_THREADS) void packed_mfma_kernel(
         const int t = e / (16 * RT), oo = e % (16 * RT), rt = oo >> 4, ii = oo & 15;
         const int64_t o = int64_t(tile) * (16 * RT) + oo;
         if (16 * tb + t < n_tok && o < c_out) {
-          float v = red[(rt * RTT + t) * PM_RED_PITCH + ii];
+          float p[2] = {0.f, 0.f};             // even and odd waves
 #pragma unroll
-          for (int w = 1; w < PM_WAVES; ++w) v += red[((w * RT + rt) * RTT + t) * PM_RED_PITCH + ii];
+          for (int w = 0; w < PM_WAVES; ++w) p[w & 1] += red[((w * RT + rt) * RTT + t) * PM_RED_PITCH + ii];
+          float v = p[0] + p[1];
           if (bias) v += sbias[nth * (16 * RT) + oo];
           const int64_t at = int64_t(16 * tb + t) * c_out + o;
           if (y_bf16) static_cast<uint16_t*>(Y)[at] = f2bf(v);
@@ -870,9 +872,22 @@ __global__ __launch_bounds__(PM_THREADS) void packed_mfma_kernel(
 // 16-row tiles, codes straight from global memory into registers) and K block
 // 2 it + w / 4 of iteration it.  The activations of an iteration's two blocks
 // are staged once for all waves, double-buffered, in the codes' pair order with
-// the slots swizzled as above; the thread that interleaves them also sums them
-// (xs per token and part), so the matrix cores run only the products.  The two
-// K halves are added through LDS at the end.
+// the slots swizzled as above.  The two K halves are added through LDS at the end.
+//
+// Groups of whole blocks (SAME): a token's outputs are the small-batch kernel's
+// bit for bit, so they do not change with the size of its batch.  xs is the same
+// product with ones, and waves w / 4 = 0 and 1 take the even and the odd
+// super-blocks in the order of the small-batch kernel's waves (0, 8, .., then 2,
+// 10, ..; 1, 9, ..), each wave's share summed on its own.  It costs: with xs
+// from the staging thread and K in sequence, 500 tokens through a 7B block's
+// linears at W4 took 445 us, now 460 (2048 tokens, 12288 x 4096, W3: 403 -> 446).
+// Shares of contiguous super-blocks cost more in the small-batch kernel (W2 g64,
+// 4 tokens: 257 -> 300 us); sums formed by one wave for the others were no faster
+// (495 us).
+//
+// Other groups: the thread that interleaves the activations also sums them (xs
+// per token and part), so the matrix cores run only the products, and K goes in
+// sequence.
 constexpr int PT_N = 128;                      // outputs per workgroup
 template <int NTB, int SUB>
 constexpr size_t tile_lds() {
@@ -888,6 +903,8 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
     const float* __restrict__ bias, int64_t c_out, void* __restrict__ Y, bool y_bf16, int ntt) {
   constexpr int TM = 16 * NTB;                 // tokens
   constexpr int XR = TM * 16 / PM_THREADS;     // staging rounds (32 tokens each)
+  constexpr bool SAME = SUB == 1;              // sums in the small-batch kernel's order
+  constexpr int KSTEP = SAME ? 2 : 1;          // blocks from kw 0's to kw 1's
   extern __shared__ uint4 lds_q[];
   char* xb = reinterpret_cast<char*>(lds_q);   // [2 buffers][TM][2 blocks][256 bytes]
   float* xsb = reinterpret_cast<float*>(xb + size_t(2) * TM * 512);   // [2][2 blocks][SUB][TM]
@@ -901,9 +918,28 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
   const int L = xcd * q8 + min(xcd, rem) + (blockIdx.x >> 3);
   const int t0 = (L % ntt) * TM;
   const int64_t o0 = int64_t(L / ntt) * PT_N + 32 * wn;
-  const int nrun = int(c_in / 32), nblk = (nrun + 3) / 4, nit = (nblk + 1) / 2;
+  const int nrun = int(c_in / 32), nblk = (nrun + 3) / 4, nsb = (nrun + 7) / 8;
+  const int nit = SAME ? 2 * ((nsb + 1) / 2) : (nblk + 1) / 2;
   const CodeMasks<BITS> cm;
   constexpr float OFF = float(1 << BITS);
+  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  // The walk over K: `b` is kw 0's block.  SAME: the blocks of super-blocks 0, 8,
+  // .. (kw 1: of the next ones), then of 2, 10, .. and so on.  True where a share
+  // ends.
+  auto next = [&](int& b) {
+    if (!SAME) {
+      b += 2;
+      return false;
+    }
+    if (!(b & 1)) {
+      ++b;
+      return false;
+    }
+    b += 2 * PM_WAVES - 1;
+    if (b < 2 * nsb) return false;
+    b = 2 * (((b >> 1) & (PM_WAVES - 1)) + 2);
+    return true;
+  };
 
   // tokens and rows past the end read zeros (and store nothing); iterations
   // past the last read nothing
@@ -916,22 +952,25 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
   const rsrc_t rh = make_rsrc(H + o0 * ng, rows * uint32_t(ng * 4)), rz = make_rsrc(Z + o0 * ng, rows * uint32_t(ng * 4));
   // staging: 16 threads per token, thread (run 0..7 of the iteration, half)
   const int srun = (tid >> 1) & 7, shalf = tid & 1, st0 = tid >> 4;
-  const uint32_t xoff = uint32_t(st0) * uint32_t(c_in * 2) + uint32_t(64 * srun + 16 * shalf);
+  const uint32_t xoff = uint32_t(st0) * uint32_t(c_in * 2) + uint32_t(256 * KSTEP * (srun >> 2) + 64 * (srun & 3) + 16 * shalf);
   const uint32_t woff = __umul24(uint32_t(i), uint32_t(nrun * BITS * 4)) + uint32_t(f * BITS * 4);
   const uint32_t goff = __umul24(uint32_t(i), uint32_t(ng * 4));
 
   uint4 slo[XR], shi[XR];
   uint32_t wn_[2][BITS], hn[2][SUB], zn[2][SUB];
-  auto issue_x = [&](int it) {
+  int bx = 0, bw = 0, bs = 0, bc = 0;           // blocks to load, to load codes of, to stage, to compute
+  auto issue_x = [&](bool any) {
 #pragma unroll
     for (int j = 0; j < XR; ++j) {
-      const uint32_t o = it < nit ? xoff + uint32_t(32 * j) * uint32_t(c_in * 2) + uint32_t(512 * it) : NONE;
+      const uint32_t o = any ? xoff + uint32_t(32 * j) * uint32_t(c_in * 2) + uint32_t(256 * bx) : NONE;
       buffer_load<4>(rx, o, reinterpret_cast<uint32_t*>(&slo[j]));
       buffer_load<4>(rx, o + 32, reinterpret_cast<uint32_t*>(&shi[j]));
     }
+    next(bx);
   };
-  auto issue_w = [&](int it) {
-    const int b = 2 * it + kw;
+  auto issue_w = [&](bool any) {
+    const int b = any ? bw + KSTEP * kw : nblk;
+    next(bw);
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
       const uint32_t wr = 16 * rt * uint32_t(nrun * BITS * 4), gr = 16 * rt * uint32_t(ng * 4);
@@ -945,9 +984,11 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
       }
     }
   };
-  auto stage = [&](int it, int buf) {
-    const bool miss = 8 * it + srun >= nrun;
-    const int blk = srun >> 2, c = 4 * (srun & 3) + 2 * shalf;
+  auto stage = [&](int buf) {
+    const int blk = srun >> 2;
+    const bool miss = 4 * (bs + KSTEP * blk) + (srun & 3) >= nrun;
+    next(bs);
+    const int c = 4 * (srun & 3) + 2 * shalf;
 #pragma unroll
     for (int j = 0; j < XR; ++j) {
       const int t = st0 + 32 * j;
@@ -957,6 +998,7 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
       char* row = xb + (size_t(buf) * TM + t) * 512 + blk * 256;
       *reinterpret_cast<uint4*>(row + 16 * (c ^ (t & 15))) = u0;
       *reinterpret_cast<uint4*>(row + 16 * ((c + 1) ^ (t & 15))) = u1;
+      if constexpr (SAME) continue;
       // this thread's 16 channels, then the part's lanes (8 / SUB of them)
       float s0 = 0.f, s1 = 0.f;
       s0 = dot2_bf16(u0.x, 0x3f803f80u, s0); s1 = dot2_bf16(u1.x, 0x3f803f80u, s1);
@@ -972,16 +1014,25 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
     }
   };
 
-  f32x4_t y[2][NTB];
+  f32x4_t y[2][NTB], total[2][NTB];            // the current share's, the finished shares'
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb) y[rt][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int tb = 0; tb < NTB; ++tb) y[rt][tb] = total[rt][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto end_share = [&]() {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        total[rt][tb] += y[rt][tb];
+        y[rt][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+  };
 
-  issue_x(0);
-  issue_w(0);
-  stage(0, 0);
-  issue_x(1);
+  issue_x(true);
+  issue_w(true);
+  stage(0);
+  issue_x(true);
   lds_barrier();
   for (int it = 0; it < nit; ++it) {
     const int buf = it & 1;
@@ -996,18 +1047,17 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
         nz[rt][u] = -(OFF + __uint_as_float(zn[rt][u]));
       }
     }
-    issue_w(it + 1);
-    if (2 * it + kw < nblk) {
+    issue_w(it + 1 < nit);
+    // (SAME: a block that is not there has step sizes and activations of zero)
+    if (SAME || bc + KSTEP * kw < nblk) {
       const char* xrow = xb + size_t(buf) * TM * 512 + kw * 256;
       const float* xsr = xsb + (buf * 2 + kw) * SUB * TM;
 #pragma unroll
       for (int u = 0; u < SUB; ++u) {
         const bool mine = SUB == 1 || f / (4 / SUB) == u;
-        f32x4_t acc[2][NTB];
+        f32x4_t acc[2][NTB], xs[NTB];
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-          for (int tb = 0; tb < NTB; ++tb) acc[rt][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int tb = 0; tb < NTB; ++tb) acc[0][tb] = acc[1][tb] = xs[tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
           const bf16x8_t q0 = code_frag<BITS>(R[0], m, cm), q1 = code_frag<BITS>(R[1], m, cm);
@@ -1019,25 +1069,27 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
             const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, v);
             acc[0][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, q0, acc[0][tb], 0, 0, 0);
             acc[1][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, q1, acc[1][tb], 0, 0, 0);
+            if constexpr (SAME) xs[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, ones, xs[tb], 0, 0, 0);
           }
         }
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
-          const float4 s = *reinterpret_cast<const float4*>(xsr + u * TM + 16 * tb + 4 * f);
-          const float xs[4] = {s.x, s.y, s.z, s.w};
+          if constexpr (!SAME) xs[tb] = *reinterpret_cast<const f32x4_t*>(xsr + u * TM + 16 * tb + 4 * f);
 #pragma unroll
           for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              y[rt][tb][r] = __builtin_fmaf(hh[rt][u], __builtin_fmaf(nz[rt][u], xs[r], acc[rt][tb][r]),
+              y[rt][tb][r] = __builtin_fmaf(hh[rt][u], __builtin_fmaf(nz[rt][u], xs[tb][r], acc[rt][tb][r]),
                                             y[rt][tb][r]);
         }
       }
     }
-    stage(it + 1, buf ^ 1);
-    issue_x(it + 2);
+    if (next(bc)) end_share();
+    stage(buf ^ 1);
+    issue_x(it + 2 < nit);
     lds_barrier();
   }
+  if (!SAME) end_share();
 
   // the second K half's sums through LDS, added to the first's
   float* red = reinterpret_cast<float*>(lds_q);   // [4 waves][2][TM][PITCH]
@@ -1048,7 +1100,7 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
       for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          red[((wn * 2 + rt) * TM + 16 * tb + 4 * f + r) * PM_RED_PITCH + i] = y[rt][tb][r];
+          red[((wn * 2 + rt) * TM + 16 * tb + 4 * f + r) * PM_RED_PITCH + i] = total[rt][tb][r];
   }
   __syncthreads();
   if (kw == 0) {
@@ -1061,7 +1113,7 @@ __global__ __launch_bounds__(PM_THREADS) void packed_tile_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int t = 16 * tb + 4 * f + r;
-          const float v = y[rt][tb][r] + red[((wn * 2 + rt) * TM + t) * PM_RED_PITCH + i] + bb;
+          const float v = total[rt][tb][r] + red[((wn * 2 + rt) * TM + t) * PM_RED_PITCH + i] + bb;
           if (t0 + t < n_tok && o < c_out) {
             const int64_t at = int64_t(t0 + t) * c_out + o;
             if (y_bf16) static_cast<uint16_t*>(Y)[at] = f2bf(v);
@@ -1171,8 +1223,9 @@ hipError_t launch_vector(const LinArgs& a, const uint16_t* X, int n_tok, void* Y
 
 // Prompts of more than 96 tokens take the tiled kernel: its time hardly grows
 // until its tiles fill the chip, while the small-batch kernel pays one pass over
-// the codes per 32 tokens (a 7B block's linears, W3 g128: 96 tokens 245 us in
-// launches of 32, 258 us tiled; 500 tokens W4: 1272 us in launches, 455 us tiled).
+// the codes per 32 tokens (a 7B block's linears as one graph, W3 g128: 96 tokens
+// 215 us in launches of 32, 97 and 128 tokens 224 us tiled; 500 tokens W4, one by
+// one: 1272 us in launches, 460 us tiled).
 constexpr int64_t TILE_TOKENS = 97;
 
 template <int BITS, int SUB>

@@ -55,6 +55,43 @@ def test_packed_linear_tile_edges(case):
     assert np.all(np.abs(Y.float().cpu().numpy().astype(np.float64) - ref) <= tol)
 
 
+# bits, c_in, group (uneven shares of K, fewer super-blocks than waves, an odd
+# number of blocks among them)
+SAME = [(4, 4096, 128), (3, 11008, 128), (2, 128, 128), (7, 384, 384), (6, 5120, 5120), (4, 1152, 128),
+        (5, 3328, 256), (3, 22016, 128)]
+
+
+def check_batches(case, c_out, sizes):
+    bits, c_in, group = case
+    most = sizes[-1]
+    q, h, z, X, B = make_linear(7, bits, most, c_out, c_in, group, True, 0)
+    Xd, Pd, hd, zd, Bd = to_dev(X, torch.bfloat16), to_dev(o_pack(q, bits)), to_dev(h), to_dev(z), to_dev(B)
+    full = oq.packed_linear(Xd, Pd, bits, group, hd, zd, Bd)
+    for n in sizes[:-1]:
+        for lo in {0, most - n}:
+            part = oq.packed_linear(Xd[lo:lo + n], Pd, bits, group, hd, zd, Bd)
+            assert torch.equal(part, full[lo:lo + n]), (n, lo)
+
+
+@pytest.mark.parametrize("c_out", [70, 16400])
+@pytest.mark.parametrize("case", SAME, ids=[f"b{c[0]}_{c[1]}_g{c[2]}" for c in SAME])
+def test_a_tokens_outputs_do_not_depend_on_its_batch(case, c_out):
+    """Groups that are a multiple of 128: kept activations (to 4 tokens), rings of
+    16, 24 and 32 tokens, several launches, one and two row tiles, whole and ragged
+    token tiles sum every product over K in the same order."""
+    if c_out > 1000 and case[1] > 6000:
+        c_out = 8200
+    check_batches(case, c_out, (1, 2, 3, 4, 5, 8, 16, 17, 24, 25, 32, 33, 40, 96, 97, 128, 200))
+
+
+@pytest.mark.parametrize("sizes", [(1, 2), (3, 4, 5, 16, 17, 32, 40, 96), (97, 128, 200)],
+                         ids=["vector", "small", "tiled"])
+@pytest.mark.parametrize("case", [(2, 5120, 64), (5, 2080, 32), (4, 288, 96)],
+                         ids=["g64", "g32_dword", "g96_dword"])
+def test_other_groups_do_not_depend_on_the_batch_within_a_kernel(case, sizes):
+    check_batches(case, 70, sizes)
+
+
 def test_a_row_of_nan_steps_leaves_the_others_alone():
     # reads past a row's end (short last block) meet the next row's step size
     q, h, z, X, _ = make_linear(77, 4, 3, 20, 160, 32, False, 0)
