@@ -2,7 +2,8 @@
 layout bit for bit, and the weight-only quantised linear element by element
 within a bound derived from its fp32 arithmetic.
 
-Bound of the linear.  The kernel forms, per run of 32 codes, p = sum x (128 + q)
+Bound of the linear.  The vector kernel (one or two tokens in groups that are no
+multiple of 128) forms, per run of 32 codes, p = sum x (128 + q)
 with bf16 x and exact bf16 codes (every product exact in fp32), then
 h * (p - (128 + z) * xs) with xs = sum x, and sums runs and lanes in fp32.  Each
 of the at most ~40 roundings on the way contributes at most 2^-24 times a
@@ -10,10 +11,13 @@ partial sum bounded by sum_c |x_c| (256 + q_c + |z_g|) h_g, so
 |Y - Y_oracle| <= 4e-6 * sum_c |x_c| (256 + q_c + |z_g|) h_g, plus half a bf16
 ulp of |Y| when Y is stored in bf16.
 
-Batches of 8 or more tokens with groups of 128 run on matrix cores: each
-group's p is a chain of four 32-term matrix products, up to 128 fp32
+Everything else runs on matrix cores, with the offset 2^bits instead of 128: each
+128-channel block's p is a chain of four 32-term matrix products, up to 128 fp32
 roundings of a partial sum bounded by the same magnitude, plus the ~40 of the
-rest: (128 + 40) 2^-24 ~ 1.0e-5 times the same sum."""
+rest: (128 + 40) 2^-24 ~ 1.0e-5 times the same sum.  The matrix instructions
+round far less often than once per term (the largest error measured is 0.01 of
+the vector kernel's bound), so only 8 or more tokens in groups of 128 are given
+that bound and all others the vector kernel's."""
 import numpy as np
 import pytest
 import torch
@@ -42,7 +46,7 @@ def make_linear(seed, bits, n_tok, c_out, c_in, group, bias, z_spread=0):
 
 
 def mfma_path(n_tok, group):
-    """The dispatch rule of oq_packed_linear: matrix cores from 8 tokens, groups of 128."""
+    """The cases that are given the matrix cores' bound."""
     return n_tok >= 8 and group == 128
 
 
@@ -73,13 +77,13 @@ LINEAR = [
     # bits, n_tok, c_out, c_in, group, bias, out dtype, z outside [0, qmax]
     (4, 1, 4096, 4096, 128, False, torch.float32, 0),     # 7B q/k/v/o shape
     (4, 1, 1000, 11008, 128, True, torch.float32, 0),     # down_proj width, ragged rows
-    (4, 2, 12289, 1024, 128, True, torch.float32, 0),     # more row pairs than resident waves
+    (4, 2, 12289, 1024, 128, True, torch.float32, 0),     # more row tiles than resident workgroups
     (3, 1, 333, 4096, 128, False, torch.float32, 0),
     (2, 1, 257, 4096, 64, False, torch.float32, 0),
     (4, 3, 129, 512, 32, True, torch.bfloat16, 2),
     (4, 8, 100, 4096, 128, False, torch.float32, 0),
-    (4, 13, 50, 1024, 1024, True, torch.float32, 0),      # 8 + 5 tokens, one group per row
-    (2, 8, 64, 11008, 128, False, torch.float32, 0),      # 8 tokens of 11008 exceed LDS: 4 + 4
+    (4, 13, 50, 1024, 1024, True, torch.float32, 0),      # one group per row
+    (2, 8, 64, 11008, 128, False, torch.float32, 0),
     (5, 2, 40, 96, 32, False, torch.float32, 3),
     (6, 5, 40, 160, 32, True, torch.float32, 0),
     (7, 4, 17, 224, 32, False, torch.bfloat16, 0),
@@ -87,10 +91,10 @@ LINEAR = [
     # groups of a number of runs that is not a power of two (3 and 344 runs)
     (4, 2, 70, 288, 96, True, torch.float32, 0),
     (3, 1, 33, 11008, 11008, False, torch.float32, 0),
-    # the widest input: one token per launch fits LDS, so 3 tokens are 3 launches
+    # the widest input: past what LDS keeps of 3 tokens
     (4, 3, 7, 65536, 128, False, torch.float32, 0),
-    # matrix cores (8+ tokens, groups of 128): 8-, 16- and 32-token launches,
-    # 70 = 64 + 6 tokens, ragged rows, the 7B shapes, every code width
+    # groups of 128: 16-, 24- and 32-token launches, 70 = 32 + 32 + 6 tokens,
+    # ragged rows, the 7B shapes, every code width
     (4, 16, 4096, 4096, 128, True, torch.float32, 0),
     (4, 64, 1000, 11008, 128, False, torch.float32, 0),
     (3, 33, 129, 11008, 128, True, torch.bfloat16, 1),
@@ -98,19 +102,18 @@ LINEAR = [
     (5, 20, 17, 256, 128, True, torch.float32, 2),
     (6, 9, 40, 384, 128, False, torch.float32, 0),
     (7, 24, 33, 128, 128, True, torch.float32, 0),
-    # the widest inputs on matrix cores: 32-token launches fill LDS exactly at
-    # 32768 channels (40 = 32 + 8); at 65536 launches take 16 tokens (20 = 16 + 4)
+    # wide inputs in launches of 32 + 8 and of 20 tokens
     (4, 40, 7, 32768, 128, True, torch.float32, 0),
     (3, 20, 5, 65536, 128, False, torch.bfloat16, 0),
-    # more 16-row workgroups than CUs (8, 12 and 40 tokens)
+    # more 16-row tiles than CUs (8, 12 and 40 tokens)
     (4, 8, 4200, 1024, 128, False, torch.float32, 0),
     (5, 12, 4113, 512, 128, True, torch.bfloat16, 1),
     (4, 40, 4352, 640, 128, True, torch.float32, 0),
-    # 16,384 rows or more: two 16-row tiles per workgroup (ragged last one)
+    # two 16-row tiles per workgroup (ragged last one)
     (4, 12, 16400, 512, 128, True, torch.bfloat16, 0),
     (3, 40, 16384, 1024, 128, False, torch.float32, 1),
     (5, 8, 16424, 384, 128, True, torch.float32, 0),
-    (4, 24, 9000, 256, 128, True, torch.float32, 0),      # from 8,192 rows at 17-32 tokens
+    (4, 24, 9000, 256, 128, True, torch.float32, 0),      # from 8,192 rows at 17-24 tokens
     (2, 20, 16400, 256, 128, False, torch.bfloat16, 1),
     (6, 8, 16390, 128, 128, True, torch.float32, 0),
     (7, 33, 16384, 384, 128, False, torch.float32, 0),
@@ -150,10 +153,10 @@ def test_packed_linear_empty_and_reproducible():
 @pytest.mark.parametrize("c_out", [260, 9000, 16400])
 def test_matrix_core_batches_give_each_token_the_same_bits(c_out):
     """On matrix cores a token's outputs depend only on its own column: a
-    token gives the same bits in batches of 8, 20 and 64.  From 16,384 rows
-    (from 8,192 in launches of 17-32 tokens) a workgroup takes two 16-row
-    tiles; its rows give the same bits as the same rows in a launch of one
-    tile per workgroup."""
+    token gives the same bits in batches of 8, 20 and 64.  Many rows (16,384;
+    12,288 in launches of 5-16 tokens, 8,192 of 17-24) make a workgroup take two
+    16-row tiles; its rows give the same bits as the same rows in a launch of
+    one tile per workgroup."""
     q, h, z, X, B = make_linear(12, 4, 64, c_out, 4096, 128, True)
     Xd, Pd, hd, zd, Bd = (to_dev(X, torch.bfloat16), to_dev(o_pack(q, 4)), to_dev(h), to_dev(z),
                           to_dev(B))
@@ -202,30 +205,30 @@ def test_pack_and_linear_agree_with_lwc_dequantised_weight():
     assert torch.all((Y.double() - ref).abs() <= 4e-6 * scale)
 
 
-@pytest.mark.parametrize("n_tok", [2, 12, 24])
-def test_packed_linear_graph_replays_match_eager(n_tok):
+@pytest.mark.parametrize("n_tok,group", [(2, 128), (12, 128), (24, 128), (2, 64)])
+def test_packed_linear_graph_replays_match_eager(n_tok, group):
     # a decode loop replays the same launches from a HIP graph: every replay,
     # with eager work and new activations between replays, matches eager runs
-    # (2 tokens: the vector kernel; 12 and 24: the matrix-core kernel)
-    q, h, z, X, B = make_linear(31, 4, n_tok, 700, 4096, 128, True)
+    # (2 tokens in groups of 64: the vector kernel; the others: matrix cores)
+    q, h, z, X, B = make_linear(31, 4, n_tok, 700, 4096, group, True)
     Xd, Pd, hd, zd, Bd = (to_dev(X, torch.bfloat16), to_dev(o_pack(q, 4)), to_dev(h), to_dev(z),
                           to_dev(B))
     Y = torch.empty((n_tok, 700), device=DEV)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
-        oq.packed_linear_into(Xd, Pd, 4, 128, hd, zd, Y, B=Bd)
+        oq.packed_linear_into(Xd, Pd, 4, group, hd, zd, Y, B=Bd)
     torch.cuda.current_stream().wait_stream(side)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        oq.packed_linear_into(Xd, Pd, 4, 128, hd, zd, Y, B=Bd)
+        oq.packed_linear_into(Xd, Pd, 4, group, hd, zd, Y, B=Bd)
     rng = np.random.default_rng(32)
     for i in range(4):
         if i:
             Xd.copy_(to_dev(bf16_round(rng.standard_normal((n_tok, 4096)).astype(np.float32)),
                             torch.bfloat16))
-        want = oq.packed_linear(Xd, Pd, 4, 128, hd, zd, Bd)
+        want = oq.packed_linear(Xd, Pd, 4, group, hd, zd, Bd)
         Y.zero_()
         torch.cuda.synchronize()
         g.replay()

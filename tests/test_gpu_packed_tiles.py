@@ -1,6 +1,6 @@
 """Packed linear: the edges of its kernels' tiles, against the oracle.
 
-Up to 96 tokens go in launches of at most 32 (4 tokens kept in LDS, 16 or 32
+Up to 96 tokens go in launches of at most 32 (4 tokens kept in LDS, 16, 24 or 32
 staged per block), more through the tiled kernel (64 tokens x 128 outputs).
 Blocks of 128 channels hold one, two or four parts by the group size; inputs
 that are no multiple of 128 channels take dword copies and a short last block.
@@ -29,7 +29,7 @@ CASES = [
     (4, 4, 17, 96, 32, True, torch.float32),           # dword copies, K shorter than the waves
     (2, 3, 50, 2080, 32, False, torch.float32),        # 65 runs: short last block
     (3, 16, 31, 2080, 160, True, torch.float32),
-    (7, 32, 33, 1056, 96, True, torch.bfloat16),       # wide codes: 32 tokens as 16 + 16
+    (7, 32, 33, 1056, 96, True, torch.bfloat16),       # wide codes: 32 tokens as 24 + 8
     (4, 32, 48, 1152, 64, True, torch.float32),        # one launch of 32, two parts
     (2, 31, 17, 2304, 128, False, torch.float32),
     (6, 17, 40, 512, 256, False, torch.float32),       # groups of two blocks
@@ -53,6 +53,40 @@ def test_packed_linear_tile_edges(case):
     if odt == torch.bfloat16:
         tol = tol + np.abs(ref) * 2.0 ** -8
     assert np.all(np.abs(Y.float().cpu().numpy().astype(np.float64) - ref) <= tol)
+
+
+# One or two tokens in groups that are no multiple of 128: the vector kernel.  A
+# wave takes row pairs in turn and each in blocks of 4096 channels, the next block
+# loading while one computes: a second, partial block, more row pairs than the
+# device's waves hold at once (8 per CU and SIMD at most: 16384 rows), and both.
+VECTOR = [
+    # bits, n_tok, c_out, c_in, group, bias, out dtype
+    (2, 1, 100, 11008, 64, False, torch.float32),      # three blocks, the last partial
+    (4, 2, 33, 11008, 64, True, torch.float32),
+    (3, 2, 41, 4128, 96, False, torch.bfloat16),       # one run past a block; 43 groups of 3 runs
+    (4, 1, 7, 8192, 32, True, torch.float32),          # two whole blocks
+    (3, 1, 40001, 160, 32, True, torch.float32),       # several row pairs a wave, odd count
+    (2, 2, 40001, 192, 96, False, torch.float32),
+    (4, 1, 33001, 4160, 64, True, torch.float32),      # both
+    (5, 2, 33001, 4128, 32, True, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("case", VECTOR, ids=[f"b{c[0]}_t{c[1]}_{c[2]}x{c[3]}_g{c[4]}" for c in VECTOR])
+def test_vector_kernel_walks(case):
+    bits, n_tok, c_out, c_in, group, bias, odt = case
+    q, h, z, X, B = make_linear(500 + VECTOR.index(case), bits, n_tok, c_out, c_in, group, bias, 0)
+    P = o_pack(q, bits)
+    Y = oq.packed_linear(to_dev(X, torch.bfloat16), to_dev(P), bits, group, to_dev(h), to_dev(z),
+                         None if B is None else to_dev(B), out_dtype=odt)
+    got = Y.float().cpu().numpy().astype(np.float64)
+    # every row where they are few, else every 97th and the first and last ones
+    rows = np.unique(np.r_[0:64, 0:c_out:97, c_out - 64:c_out]) if c_out > 1000 else np.arange(c_out)
+    ref = o_linear(X, P[rows], bits, group, h[rows], z[rows], None if B is None else B[rows])
+    tol = bound(q[rows], h[rows], z[rows], X, group)
+    if odt == torch.bfloat16:
+        tol = tol + np.abs(ref) * 2.0 ** -8
+    assert np.all(np.abs(got[:, rows] - ref) <= tol)
 
 
 # bits, c_in, group (uneven shares of K, fewer super-blocks than waves, an odd
