@@ -12,25 +12,27 @@ from tests.cases import dev, make_problem, normwise, small_llama
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # tokens, hidden, ffn, kv rows, bits, group, LET, activation bits
-    (8, 128, 256, 128, 4, 64, False, 16),        # less than one stage
-    (72, 128, 256, 72, 3, 128, False, 16),       # one stage and 8 rows
-    (120, 256, 512, 200, 4, None, True, 4),      # ragged stacked rows too
-    (1016, 256, 512, 256, 2, 64, False, 16),
-    (4104, 256, 512, 256, 4, None, True, 16),    # K split (4160 tokens of stages)
-    (2040, 256, 768, 8, 4, 32, False, 16),
+CASES = [  # tokens, hidden, ffn, kv rows, bits, group, LET, activation bits, K splits of the weight gradient
+    (8, 128, 256, 128, 4, 64, False, 16, 1),     # less than one stage
+    (72, 128, 256, 72, 3, 128, False, 16, 1),    # one stage and 8 rows
+    (120, 256, 512, 200, 4, None, True, 4, 1),   # ragged stacked rows too
+    (1016, 256, 512, 256, 2, 64, False, 16, 1),
+    (4104, 256, 512, 256, 4, None, True, 16, 1),  # 65 stages: no split
+    (2040, 256, 768, 8, 4, 32, False, 16, 2),
+    (4088, 256, 512, 200, 4, None, True, 4, 4),  # ragged rows and tokens, parts summed by the LET backward
+    (2040, 256, 512, 256, 4, None, True, 16, 2),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[f"t{c[0]}_h{c[1]}_kv{c[3]}_g{c[5]}{'_let' if c[6] else ''}" for c in CASES])
 def test_ragged_step_matches_oracle(case):
-    T, hidden, ffn, kv, bits, group, let, act = case
+    T, hidden, ffn, kv, bits, group, let, act, splits = case
     w = small_llama("ragged", hidden=hidden, ffn=ffn, T=T, w_bits=bits, group=group, kv=kv, let=let, act_bits=act)
     P = make_problem(w, seed=5, logit="random")
     dt = torch.bfloat16
     blk = oq.Block(T, [(s.width, s.let, s.act_bits) for s in w.sites],
                    [(l.site, l.c_out, l.bits, l.group) for l in w.linears], dtype=dt)
-    assert all(p["direct"] for p in blk.plan())
+    assert all(p["direct"] and p["wgrad_splits"] == splits for p in blk.plan())
     blk.ws.fill_(0xFF)                            # NaN everywhere a pad is forgotten
     opt = lambda xs: [None if x is None else dev(x) for x in xs]
     # X ends where its allocation's tokens do: the rows after it are NaN
