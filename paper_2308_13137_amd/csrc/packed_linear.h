@@ -6,7 +6,7 @@
 //                         cores fed by asynchronous copies, bound by the stream
 //                         of codes at few tokens
 //   packed_tile_kernel    more tokens: a tiled product
-//   packed_linear_kernel  one or two tokens with groups of 32 or 64 channels
+//   packed_linear_kernel  one or two tokens with groups that are no multiple of 128
 //
 // No kernel rounds a weight: codes enter the products as exact small integers in
 // bf16, and step sizes and zero points multiply fp32 sums.  Measured over a 7B
@@ -242,7 +242,7 @@ OQ_DEV void code_pairs(const uint32_t* w, uint32_t* p, uint32_t mask, uint32_t m
 }
 
 // ------------------------------------------------------------------ one or two tokens, small groups
-// Groups of 32 or 64 channels at one or two tokens: a product per part would
+// Groups that are no multiple of 128 (32, 64, 96, ..) at one or two tokens: a product per part would
 // leave the matrix cores mostly zeros, so the dot-product unit takes the runs
 // one by one (4096 channels, W4, one token, groups of 32: 43.9 us over a 7B
 // block's linears, 61.6 us on matrix cores; groups of 64: 35.7 against 48.5 us
@@ -531,6 +531,8 @@ struct MfmaCfg {
   static constexpr int SLOT = WB + HZ * 4 + XB;            // ring slot, bytes
   static constexpr int RED = PM_WAVES * RT * (TT < 16 ? TT : 16) * PM_RED_PITCH * 4;
   static constexpr int NRED = TT > 16 ? 1 : 2;             // partial-output buffers
+  // whether a workgroup can run at all: two-slot rings and partial outputs in LDS
+  static constexpr bool FITS = size_t(PM_WAVES) * 2 * SLOT + size_t(NRED) * RED <= PL_LDS_MAX;
   // LDS of the workgroup: rings, kept activations, partial outputs, biases
   static size_t lds(int depth, int64_t c_in, int n_tok, bool bias) {
     const size_t sb = size_t((c_in + 255) / 256);
@@ -1173,9 +1175,11 @@ hipError_t launch_mfma(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) 
 // hide (four: 40.1 -> 44.7 us over a 7B block's linears).
 template <int BITS, int TT, int SUB>
 hipError_t launch_mfma_rt(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) {
-  // rows that are no whole 16-byte chunks: dword copies
-  if (a.c_in % PM_BLOCK) return launch_mfma<BITS, TT, 1, SUB, 2, false>(a, X, n_tok, Y);
-  if constexpr (TT < 32) {
+  // rows that are no whole 16-byte chunks (never with whole blocks): dword copies
+  if constexpr (SUB > 1) {
+    if (a.c_in % PM_BLOCK) return launch_mfma<BITS, TT, 1, SUB, 2, false>(a, X, n_tok, Y);
+  }
+  if constexpr (TT < 32 && MfmaCfg<BITS, TT, 2, SUB>::FITS) {
     const int64_t from = SUB == 2 ? 4096 : TT == 4 ? 16384 : TT == 16 ? 12288 : 8192;
     if (a.c_out >= from && MfmaCfg<BITS, TT, 2, SUB>::lds(2, a.c_in, n_tok, a.bias != nullptr) <= PL_LDS_MAX)
       return launch_mfma<BITS, TT, 2, SUB, 2, true>(a, X, n_tok, Y);
@@ -1238,7 +1242,8 @@ hipError_t linear_sub(const LinArgs& a, const uint16_t* X, int64_t n_tok, void* 
   for (int64_t t0 = 0; t0 < n_tok;) {
     int take = int(std::min<int64_t>(n_tok - t0, 32));
     // 32 tokens where their rings fit LDS (not with wide codes), else 24
-    if (take > 24 && MfmaCfg<BITS, 32, 1, SUB>::lds(2, a.c_in, take, bias) > PL_LDS_MAX) take = 24;
+    constexpr bool T32 = MfmaCfg<BITS, 32, 1, SUB>::FITS;
+    if (take > 24 && (!T32 || MfmaCfg<BITS, 32, 1, SUB>::lds(2, a.c_in, take, bias) > PL_LDS_MAX)) take = 24;
     const uint16_t* x = X + t0 * a.c_in;
     void* y = static_cast<char*>(Y) + size_t(t0) * size_t(a.c_out) * es;
     // up to 4 tokens are kept in LDS where they fit
@@ -1246,7 +1251,7 @@ hipError_t linear_sub(const LinArgs& a, const uint16_t* X, int64_t n_tok, void* 
     const hipError_t e = keep         ? launch_mfma_rt<BITS, 4, SUB>(a, x, take, y)
                          : take <= 16 ? launch_mfma_rt<BITS, 16, SUB>(a, x, take, y)
                          : take <= 24 ? launch_mfma_rt<BITS, 24, SUB>(a, x, take, y)
-                                      : launch_mfma_rt<BITS, 32, SUB>(a, x, take, y);
+                                      : launch_mfma_rt<BITS, T32 ? 32 : 24, SUB>(a, x, take, y);
     if (e != hipSuccess) return e;
     t0 += take;
   }
