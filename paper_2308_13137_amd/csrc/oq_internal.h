@@ -124,7 +124,7 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
                    bool dq_bf16, uint8_t* codes, float* h, float* z, hipStream_t st,
                    float4* gstat = nullptr, int quant = 0);
 // LWC forward straight to the deployed bit strings (bits 2..7, c_in a multiple
-// of 32), with h and z, where lwc_pack_supported.
+// of 32, groups of at least 32), with h and z, where lwc_pack_supported.
 bool lwc_pack_supported(int64_t c_in, int64_t group, bool has_s, int quant);
 hipError_t lwc_fwd_pack(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, const float* s,
                         const float* gl, const float* bl, int bits, int64_t group, uint8_t* packed,

@@ -1160,7 +1160,7 @@ __global__ __launch_bounds__(NTB, LET && KC == 2 && NTB == 256 ? 3 : 1) void act
   const int64_t r1 = min(T, r0 + R);
   // with LET and up to two chunks per thread, the next row's X and dX^ are
   // loaded while this row is reduced (wider rows would spill; without LET a
-  // block has one row)
+  // block has one row, or a few where there are more than ROW_BLOCKS)
   constexpr bool PF = LET && KC <= 2;
   Chunk8<TX> xn[KC];
   float gn[KC][8];
@@ -1512,7 +1512,7 @@ hipError_t lwc_fwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
 // The codes packed as they are formed (W^ is not wanted), where the kernels
 // that walk whole rows or small groups without s take the shape.
 bool lwc_pack_supported(int64_t c_in, int64_t group, bool has_s, int quant) {
-  if (quant != WQ_LWC || c_in % 32) return false;
+  if (quant != WQ_LWC || c_in % 32 || group < 32) return false;   // (smaller groups are not deployed)
   return (small_group(group) && !has_s) || (group == c_in && (c_in / 8 + 63) / 64 <= 32);
 }
 
@@ -1533,8 +1533,6 @@ hipError_t lwc_fwd_pack(const void* W, bool w_bf16, int64_t c_out, int64_t c_in,
     };
     auto by_g = [&](auto tw) {
       switch (group / 8) {
-        case 1: go(tw, std::integral_constant<int, 1>{}); break;
-        case 2: go(tw, std::integral_constant<int, 2>{}); break;
         case 4: go(tw, std::integral_constant<int, 4>{}); break;
         case 8: go(tw, std::integral_constant<int, 8>{}); break;
         case 16: go(tw, std::integral_constant<int, 16>{}); break;
@@ -1783,7 +1781,7 @@ hipError_t act_bwd(const void* X, bool x_bf16, int64_t T, int64_t C, int bits, c
   if (C <= 0 || C % 8 || kc == 0) return hipErrorInvalidValue;
   if (T <= 0) return hipSuccess;
   const bool let = s || delta || p_sx || p_s1;
-  // (one block per row as long as the grid's threads stay below 2^32)
+  // (without LET one block per row up to ROW_BLOCKS rows: at most 2^29 threads)
   const int R = let ? rows_per_block(T, ACT_BLOCKS) : rows_per_block(T, ROW_BLOCKS);
   const dim3 grid(unsigned((T + R - 1) / R));
   auto launch = [&](auto tx, auto kcc, auto nt, auto lt) {
