@@ -1373,7 +1373,11 @@ __global__ __launch_bounds__(64) void gemm_f32_small_kernel(const float* __restr
 }
 
 // Fewer than 256 tiles of 64 x 64 (less than one per compute unit): the wave
-// tiles.  Their operands are addressed in 31 bits.
+// tiles.  The tile kernel's time is then one workgroup's walk along K, whatever
+// the tiles; up to the edge the wave tiles are faster (128 x 256 x 256: 17.1 -> 4.5
+// us, 512 x 512 x 512: 31.6 -> 10.0, 960 x 960 x 960 and 4096: 63.0 -> 54.2 and 251
+// -> 213, 64 x 16320 x 512: 35.6 -> 32.7; a calibration step of 960 x 960 at 960
+// tokens: 157 -> 112).  Their operands are addressed in 31 bits.
 bool f32_small(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   const int64_t tiles = ((M + F32_TILE - 1) / F32_TILE) * ((N + F32_TILE - 1) / F32_TILE);
   const int64_t most = int64_t(1) << 29;
