@@ -21,7 +21,6 @@ CASES = [dict(S=64, ns=3, H=1, Hkv=1), dict(S=320, ns=2, H=5, Hkv=5), dict(S=192
 @pytest.mark.parametrize("d", (64, 128))
 @pytest.mark.parametrize("c", CASES, ids=[str(c) for c in CASES])
 def test_attention_tiles(c, d):
-    print(f"attention tiles {c} d={d}", flush=True)
     S, H, Hkv, T = c["S"], c["H"], c["Hkv"], c["S"] * c["ns"]
     rng = np.random.default_rng(31 + S + d + H)
     q, do = (bf16_exact(rng.standard_normal((T, H * d))) for _ in range(2))

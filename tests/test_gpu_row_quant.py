@@ -22,7 +22,6 @@ def bits_equal(a, b):
 @pytest.mark.parametrize("C", WIDTHS)
 @pytest.mark.parametrize("dtype", (torch.float32, torch.bfloat16))
 def test_activations_without_let(C, dtype):
-    print(f"row quantisers C={C} {dtype}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(C)
     T = 5
     X = torch.randn(T, C, generator=gen, device="cuda").to(dtype)
@@ -45,7 +44,6 @@ def test_activations_without_let(C, dtype):
 
 @pytest.mark.parametrize("c_in", WIDTHS[3:])
 def test_row_weights_without_let(c_in):
-    print(f"row weight gradients c_in={c_in}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(c_in)
     n = 7
     W = (0.02 * torch.randn(n, c_in, generator=gen, device="cuda")).bfloat16()
