@@ -39,7 +39,7 @@ COPY_BYTES = 1 << 30          # calibration copy: 1 GiB read, 1 GiB written
 # sources whose text defines the packed linear's kernels
 PACKED_SOURCES = ("paper_2308_13137_amd/csrc/packed.hip", "paper_2308_13137_amd/csrc/packed.h",
                   "paper_2308_13137_amd/csrc/packed_linear.h", "paper_2308_13137_amd/csrc/common.h")
-PACKED_KERNELS = ("packed_linear_kernel", "packed_mfma_kernel", "packed_tile_kernel")
+PACKED_KERNELS = ("packed_linear_kernel", "packed_mfma_kernel", "packed_wide_kernel", "packed_tile_kernel")
 # per dominant kernel: its sources, the key of their hash in the summary, the
 # dispatches the counters are read from, and what they are called
 TRAFFIC_KINDS = {

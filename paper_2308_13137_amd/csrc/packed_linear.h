@@ -5,6 +5,7 @@
 //   packed_mfma_kernel    up to 96 tokens, in launches of at most 32: matrix
 //                         cores fed by asynchronous copies, bound by the stream
 //                         of codes at few tokens
+//   packed_wide_kernel    25 to 32 of them where rows are many or codes wide
 //   packed_tile_kernel    more tokens: a tiled product
 //   packed_linear_kernel  one or two tokens with groups that are no multiple of 128
 //
@@ -542,7 +543,7 @@ struct MfmaCfg {
   }
 };
 
-// TT: tokens staged (4, 16, 24 or 32).  A16: rows of whole 16-byte chunks (c_in a
+// TT: tokens staged (4, 8, 16, 24 or 32).  A16: rows of whole 16-byte chunks (c_in a
 // multiple of 128), else dword copies.
 template <int BITS, int TT, int RT, int SUB, int D, bool A16>
 __global__ __launch_bounds__(PM_THREADS) void packed_mfma_kernel(
@@ -868,6 +869,162 @@ __global__ __launch_bounds__(PM_THREADS) void packed_mfma_kernel(
   }
 }
 
+// ------------------------------------------------------------------ 17 to 32 tokens, many rows
+// The small-batch kernel's product where the rings of 32 tokens leave LDS no room
+// for two row tiles (or, with 6- and 7-bit codes, for one): only the activations
+// go through LDS, a block ahead, and a lane's codes, step size and zero point
+// through registers.  Groups of whole blocks; shares of K, arithmetic and order of
+// the sums are the small-batch kernel's, so the outputs are the same bits.
+// (W6, 32 tokens, 24576 x 8192: 110 us in launches of 24 and 8, 76 here.)
+constexpr int PW_TOKENS = 32;
+
+template <int BITS, int RT>
+__global__ __launch_bounds__(PM_THREADS) void packed_wide_kernel(
+    const uint16_t* __restrict__ X, int n_tok, int64_t c_in, const uint32_t* __restrict__ packed,
+    int ng, uint32_t group_inv, const float* __restrict__ H, const float* __restrict__ Z,
+    const float* __restrict__ bias, int64_t c_out, void* __restrict__ Y, bool y_bf16) {
+  constexpr int NTB = 2, XB = PW_TOKENS * 256;   // bytes of a block's activations
+  extern __shared__ uint4 lds_q[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f = lane >> 4, i = lane & 15;
+  const int nrun = int(c_in / 32), nsb = (nrun + 7) / 8, nblk = nrun / 4;
+  const int64_t o0 = int64_t(blockIdx.x) * (16 * RT);
+  char* ring = reinterpret_cast<char*>(lds_q) + wave * (2 * XB);
+  const uint32_t ring_a = lds_addr(ring);
+  const CodeMasks<BITS> cm;
+  constexpr float OFF = float(1 << BITS);
+  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  // this lane's rows (rows past c_out re-read the last one and store nothing)
+  const uint32_t* prow[RT];
+  const float *hrow[RT], *zrow[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int64_t row = std::min<int64_t>(o0 + 16 * rt + i, c_out - 1);
+    prow[rt] = packed + (row * nrun + f) * BITS;
+    hrow[rt] = H + row * ng;
+    zrow[rt] = Z + row * ng;
+  }
+  // block b's activations into buffer `s`: a copy takes four tokens' 256 bytes,
+  // chunk c of token t at c ^ (t % 16); tokens past n_tok re-read the last one
+  auto copy_x = [&](int b, int s) {
+#pragma unroll
+    for (int j = 0; j < PW_TOKENS / 4; ++j) {
+      if (4 * j >= n_tok) break;               // uniform
+      const int t = 4 * j + f, c = i ^ (t & 15);
+      const uint32_t off = uint32_t(min(t, n_tok - 1)) * uint32_t(c_in * 2) + uint32_t(b * 256 + 16 * c);
+      copy16_lds(X, off, ring_a + uint32_t(s * XB + 1024 * j));
+    }
+  };
+  uint32_t wn[RT][BITS];
+  float hn[RT], zn[RT];
+  auto load_w = [&](int b) {
+    const int g = group_of(4 * b, group_inv);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      load_run<BITS>(prow[rt] + b * (4 * BITS), wn[rt]);
+      hn[rt] = hrow[rt][g];
+      zn[rt] = zrow[rt][g];
+    }
+  };
+  // the wave's blocks: both of super-blocks wave, wave + 8, ..
+  auto next = [&](int b) { return b & 1 ? b + 2 * PM_WAVES - 1 : b + 1; };
+
+  f32x4_t y[RT][NTB];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb) y[rt][tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  int b = 2 * wave, s = 0;
+  if (b < nblk) {
+    copy_x(b, 0);
+    load_w(b);
+  }
+  for (; b < nblk; s ^= 1) {
+    wait_vm<0>();                              // block b, issued one turn ago, has landed
+    uint32_t R[RT][BITS];
+    float hh[RT], nz[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      interleave_run<BITS>(wn[rt], R[rt]);
+      hh[rt] = hn[rt];
+      nz[rt] = -(OFF + zn[rt]);
+    }
+    // (the last block of K may be the first of its super-block)
+    const int b2 = next(b);
+    if (b2 < nblk) {
+      wait_lds_reads();                        // the buffer's former block has been read
+      copy_x(b2, s ^ 1);
+      load_w(b2);
+    }
+    f32x4_t acc[RT][NTB], xs[NTB];
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb) {
+      xs[tb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt][tb] = xs[tb];
+    }
+    const char* xb = ring + s * XB + i * 256;
+    bf16x8_t xf[NTB][4];
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) {
+        uint4 u0, u1;
+        interleave_x(*reinterpret_cast<const uint4*>(xb + tb * 4096 + 16 * ((4 * f + mm) ^ i)),
+                     *reinterpret_cast<const uint4*>(xb + tb * 4096 + 16 * ((4 * f + 2 + mm) ^ i)), u0, u1);
+        xf[tb][2 * mm] = __builtin_bit_cast(bf16x8_t, u0);
+        xf[tb][2 * mm + 1] = __builtin_bit_cast(bf16x8_t, u1);
+      }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb)
+        xs[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[tb][m], ones, xs[tb], 0, 0, 0);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const bf16x8_t q = code_frag<BITS>(R[rt], m, cm);
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb)
+          acc[rt][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[tb][m], q, acc[rt][tb], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          y[rt][tb][r] = __builtin_fmaf(hh[rt], __builtin_fmaf(nz[rt], xs[tb][r], acc[rt][tb][r]), y[rt][tb][r]);
+    b = b2;
+  }
+  // the waves' partial outputs (lane (f, i): tokens 16 tb + 4 f + r of row 16 rt +
+  // i) take the buffers' place: every copy has landed and been read
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(lds_q);   // [PM_WAVES][RT][32 tokens][PITCH]
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[((wave * RT + rt) * PW_TOKENS + 16 * tb + 4 * f + r) * PM_RED_PITCH + i] = y[rt][tb][r];
+  __syncthreads();
+  for (int e = tid; e < 16 * RT * PW_TOKENS; e += PM_THREADS) {
+    const int t = e / (16 * RT), oo = e % (16 * RT), rt = oo >> 4, ii = oo & 15;
+    const int64_t o = o0 + oo;
+    if (t < n_tok && o < c_out) {
+      float p[2] = {0.f, 0.f};                 // even and odd waves
+#pragma unroll
+      for (int w = 0; w < PM_WAVES; ++w) p[w & 1] += red[((w * RT + rt) * PW_TOKENS + t) * PM_RED_PITCH + ii];
+      const float v = p[0] + p[1] + (bias ? bias[o] : 0.f);
+      const int64_t at = int64_t(t) * c_out + o;
+      if (y_bf16) static_cast<uint16_t*>(Y)[at] = f2bf(v);
+      else static_cast<float*>(Y)[at] = v;
+    }
+  }
+}
+
 // ------------------------------------------------------------------ prompts
 // The same product as a tiled one for many tokens.  A workgroup of eight waves
 // owns 128 outputs x 16 NTB tokens: wave w takes outputs 32 (w % 4) .. + 31 (two
@@ -1167,12 +1324,16 @@ hipError_t launch_mfma(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) 
 
 // Two row tiles per workgroup share a block's activations and their sums (4096
 // channels, W3 g128, one token, 22016 rows: 16.4 -> 13.9 us), but halve the
-// workgroups: from 16384 rows, or from 12288 where more than 4 tokens make the
+// workgroups: from 16384 rows, or from 12288 where more than 8 tokens make the
 // activations dearer (12 tokens: 12.9 -> 12.3 us), or 4096 where two parts per
 // block double that work (W2 g64, 4 tokens, 5120 rows: 11.1 -> 9.7 us); fewer
-// rows measured slower (4096 rows, g128, one token: 6.0 -> 7.2 us).  The rings
-// are two units deep: deeper ones cost more in resident workgroups than they
-// hide (four: 40.1 -> 44.7 us over a 7B block's linears).
+// rows measured slower (4096 rows, g128, one token: 6.0 -> 7.2 us).  One token
+// leaves little to share and takes one tile, except at 3 bits (44032 x 8192: W4
+// 46.6 -> 42.1 us, W6 67.7 -> 59.2, W2 35.5 -> 33.2; W3 42.7 with two, 44.5 with one).
+// 5 to 8 tokens have rings of their own (12288 x 4096, W4, 8 tokens: 14.3 us in rings
+// of 16 tokens, 11.7 in rings of 8; two tiles 13.1; 13824 x 5120: one 17.8, two 16.4).
+// The rings are two units deep: deeper ones cost
+// more in resident workgroups than they hide (four: 40.1 -> 44.7 us over a 7B block's linears).
 template <int BITS, int TT, int SUB>
 hipError_t launch_mfma_rt(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) {
   // rows that are no whole 16-byte chunks (never with whole blocks): dword copies
@@ -1180,11 +1341,39 @@ hipError_t launch_mfma_rt(const LinArgs& a, const uint16_t* X, int n_tok, void* 
     if (a.c_in % PM_BLOCK) return launch_mfma<BITS, TT, 1, SUB, 2, false>(a, X, n_tok, Y);
   }
   if constexpr (TT < 32 && MfmaCfg<BITS, TT, 2, SUB>::FITS) {
-    const int64_t from = SUB == 2 ? 4096 : TT == 4 ? 16384 : TT == 16 ? 12288 : 8192;
-    if (a.c_out >= from && MfmaCfg<BITS, TT, 2, SUB>::lds(2, a.c_in, n_tok, a.bias != nullptr) <= PL_LDS_MAX)
+    const bool one = TT == 4 && SUB == 1 && BITS != 3 && n_tok == 1;
+    const int64_t from = SUB == 2 ? 4096 : TT == 4 ? 16384 : TT == 8 ? 13312 : TT == 16 ? 12288 : 8192;
+    if (!one && a.c_out >= from && MfmaCfg<BITS, TT, 2, SUB>::lds(2, a.c_in, n_tok, a.bias != nullptr) <= PL_LDS_MAX)
       return launch_mfma<BITS, TT, 2, SUB, 2, true>(a, X, n_tok, Y);
   }
   return launch_mfma<BITS, TT, 1, SUB, 2, true>(a, X, n_tok, Y);
+}
+
+template <int BITS, int RT>
+hipError_t launch_wide(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) {
+  auto k = packed_wide_kernel<BITS, RT>;
+  constexpr size_t lds = size_t(PM_WAVES) * 2 * PW_TOKENS * 256;
+  static_assert(lds >= size_t(PM_WAVES) * RT * PW_TOKENS * PM_RED_PITCH * 4, "partial outputs");
+  int n = 0;
+  const hipError_t e = resident(reinterpret_cast<const void*>(k), PM_THREADS, lds, &n);   // (allows the LDS)
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(unsigned((a.c_out + 16 * RT - 1) / (16 * RT))), dim3(PM_THREADS), lds, a.stream, X,
+                     n_tok, a.c_in, a.packed, a.ng, a.group_inv, a.h, a.z, a.bias, a.c_out, Y, a.y_bf16);
+  return hipGetLastError();
+}
+
+// 25 to 32 tokens in groups of whole blocks: whether two row tiles per workgroup
+// pay.  One workgroup with 32 tokens' activations fits a compute unit, so 256 run
+// at a time, and two tiles take about 7/4 of a ring workgroup's time (3/2 of one's
+// through registers, the only way with 6 and 7 bits): 8192 rows of 8192 channels
+// are one round of the two-tile kernel instead of two (W4, 32 tokens: 25.0 -> 21.5
+// us; 22016 x 4096: 38.7 -> 31.7), 12288 rows two instead of three (W2 x 4096: 17.3
+// -> 19.3), 4096 rows one as well (W4 x 11008: 18 -> 24.6).
+int64_t rounds_of(int64_t c_out, int rows) { return ((c_out + rows - 1) / rows + 255) / 256; }
+template <int BITS>
+bool two_tiles(int64_t c_out) {
+  const int64_t two = rounds_of(c_out, 32), one = rounds_of(c_out, 16);
+  return BITS >= 6 ? 3 * two < 2 * one : 7 * two < 4 * one;
 }
 
 template <int BITS, int NTB, int SUB>
@@ -1241,14 +1430,24 @@ hipError_t linear_sub(const LinArgs& a, const uint16_t* X, int64_t n_tok, void* 
     return n_tok == 1 ? launch_vector<BITS, 1>(a, X, 1, Y) : launch_vector<BITS, 2>(a, X, 2, Y);
   for (int64_t t0 = 0; t0 < n_tok;) {
     int take = int(std::min<int64_t>(n_tok - t0, 32));
+    // 33 to 48 tokens at 6 and 7 bits where two row tiles save few rounds: 24 and the
+    // rest (27648 x 5120, 48 tokens: 96 us, 105 as 32 and 16; 24576 x 8192: 130 and 115)
+    if (SUB == 1 && BITS >= 6 && n_tok - t0 > 32 && n_tok - t0 <= 48 &&
+        9 * rounds_of(a.c_out, 32) > 5 * rounds_of(a.c_out, 16))
+      take = 24;
     // 32 tokens where their rings fit LDS (not with wide codes), else 24
-    constexpr bool T32 = MfmaCfg<BITS, 32, 1, SUB>::FITS;
-    if (take > 24 && (!T32 || MfmaCfg<BITS, 32, 1, SUB>::lds(2, a.c_in, take, bias) > PL_LDS_MAX)) take = 24;
+    constexpr bool T32 = MfmaCfg<BITS, 32, 1, SUB>::FITS && !(SUB == 1 && BITS >= 6);
+    // (through registers also where codes are too wide for rings of 32: 6 and 7 bits, 32 tokens, 4096 x 4096
+    // 13.4 us in launches of 24 and 8, 9.0 in one)
+    const bool two = two_tiles<BITS>(a.c_out), wide = SUB == 1 && take > 24 && (BITS >= 6 || two);
+    if (!wide && take > 24 && (!T32 || MfmaCfg<BITS, 32, 1, SUB>::lds(2, a.c_in, take, bias) > PL_LDS_MAX)) take = 24;
     const uint16_t* x = X + t0 * a.c_in;
     void* y = static_cast<char*>(Y) + size_t(t0) * size_t(a.c_out) * es;
     // up to 4 tokens are kept in LDS where they fit
     const bool keep = take <= 4 && MfmaCfg<BITS, 4, 1, SUB>::lds(2, a.c_in, take, bias) <= PL_LDS_MAX;
     const hipError_t e = keep         ? launch_mfma_rt<BITS, 4, SUB>(a, x, take, y)
+                         : wide       ? (BITS >= 6 && !two ? launch_wide<BITS, 1>(a, x, take, y) : launch_wide<BITS, 2>(a, x, take, y))
+                         : take <= 8  ? launch_mfma_rt<BITS, 8, SUB>(a, x, take, y)
                          : take <= 16 ? launch_mfma_rt<BITS, 16, SUB>(a, x, take, y)
                          : take <= 24 ? launch_mfma_rt<BITS, 24, SUB>(a, x, take, y)
                                       : launch_mfma_rt<BITS, T32 ? 32 : 24, SUB>(a, x, take, y);

@@ -7,7 +7,7 @@ where a copy is issued (the copy may be into the slot that the read is from), an
 no vector instruction may write a scalar register that a copy in an asm block
 reads less than five wait states later (the compiler's own hazard handling does
 not look into asm blocks).  Both are checked on the machine code of the packed
-linear's small-batch kernel, over every path through it."""
+linear's small-batch kernels, over every path through them."""
 import os
 import re
 import subprocess
@@ -16,8 +16,9 @@ import pytest
 
 from paper_2308_13137_amd import build
 
+WIDE = [(2, 2), (6, 1), (7, 2)]  # BITS, RT of the kernel for many rows
 INSTANCES = [  # BITS, TT, RT, SUB, 16-byte copies
-    (4, 4, 1, 1, True), (2, 4, 2, 2, True), (3, 4, 1, 4, False), (7, 4, 1, 4, True), (4, 16, 2, 1, True),
+    (4, 4, 1, 1, True), (2, 4, 2, 2, True), (3, 4, 1, 4, False), (7, 4, 1, 4, True), (4, 16, 2, 1, True), (6, 8, 1, 2, True),
     (3, 24, 1, 1, True), (5, 16, 1, 2, False), (4, 32, 1, 2, True),
 ]
 
@@ -168,14 +169,15 @@ def test_the_scan_finds_what_it_looks_for():
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
 def test_refills_of_the_packed_linears_rings_follow_the_slots_reads(tmp_path):
     src = tmp_path / "instances.hip"
-    src.write_text(SOURCE % "\n".join(
-        f"  e = launch_mfma<{b}, {tt}, {rt}, {sub}, 2, {str(a16).lower()}>(a, X, {min(tt, 4)}, Y);"
-        for b, tt, rt, sub, a16 in INSTANCES))
+    calls = [f"  e = launch_mfma<{b}, {tt}, {rt}, {sub}, 2, {str(a16).lower()}>(a, X, {min(tt, 4)}, Y);"
+             for b, tt, rt, sub, a16 in INSTANCES]
+    calls += [f"  e = launch_wide<{b}, {rt}>(a, X, 32, Y);" for b, rt in WIDE]
+    src.write_text(SOURCE % "\n".join(calls))
     asm = tmp_path / "instances.s"
     subprocess.run([build.HIPCC, *build.FLAGS, "-Wno-everything", "--cuda-device-only", "-S", str(src), "-o", str(asm)],
                    check=True, timeout=600)
-    found = {k: findings(v) for k, v in kernels(asm.read_text()).items() if "packed_mfma_kernel" in k}
-    assert len(found) == len(INSTANCES)
+    found = {k: findings(v) for k, v in kernels(asm.read_text()).items() if "packed_mfma_kernel" in k or "packed_wide_kernel" in k}
+    assert len(found) == len(INSTANCES) + len(WIDE)
     for name, (copies, unordered, hazards) in found.items():
         assert copies > 0, name
         assert not unordered, (name, unordered[:3], len(unordered))

@@ -1,6 +1,6 @@
 """Packed linear: the edges of its kernels' tiles, against the oracle.
 
-Up to 96 tokens go in launches of at most 32 (4 tokens kept in LDS, 16, 24 or 32
+Up to 96 tokens go in launches of at most 32 (4 tokens kept in LDS, 8, 16, 24 or 32
 staged per block), more through the tiled kernel (64 tokens x 128 outputs).
 Blocks of 128 channels hold one, two or four parts by the group size; inputs
 that are no multiple of 128 channels take dword copies and a short last block.
@@ -37,6 +37,15 @@ CASES = [
     (4, 2, 16400, 256, 128, True, torch.float32),
     (5, 5, 12304, 384, 32, False, torch.float32),
     (4, 4, 70, 22016, 128, False, torch.float32),      # 4 tokens past what LDS keeps
+    (5, 6, 40, 640, 64, True, torch.float32),          # rings of 8 tokens, two parts
+    (7, 8, 33, 1056, 32, False, torch.bfloat16),       # and by dword copies
+    (4, 5, 13320, 256, 128, True, torch.float32),      # and two row tiles
+    (4, 27, 5130, 384, 128, True, torch.float32),      # codes through registers: ragged rows and tokens, odd block count
+    (3, 32, 5121, 128, 128, False, torch.bfloat16),    # one block: seven waves without one
+    (2, 25, 5152, 2304, 768, False, torch.float32),
+    (7, 32, 33, 1152, 128, True, torch.float32),       # one row tile at wide codes
+    (6, 29, 5136, 512, 256, False, torch.bfloat16),
+    (6, 45, 64, 384, 128, True, torch.float32),        # 24 + 21 tokens
 ]
 
 
@@ -107,13 +116,14 @@ def check_batches(case, c_out, sizes):
             assert torch.equal(part, full[lo:lo + n]), (n, lo)
 
 
-@pytest.mark.parametrize("c_out", [70, 16400])
+@pytest.mark.parametrize("c_out", [70, 5130, 16400])
 @pytest.mark.parametrize("case", SAME, ids=[f"b{c[0]}_{c[1]}_g{c[2]}" for c in SAME])
 def test_a_tokens_outputs_do_not_depend_on_its_batch(case, c_out):
     """Groups that are a multiple of 128: kept activations (to 4 tokens), rings of
-    16, 24 and 32 tokens, several launches, one and two row tiles, whole and ragged
+    8, 16, 24 and 32 tokens, codes through registers (25 to 32 tokens of 5130 rows
+    or at 6 and 7 bits), several launches, one and two row tiles, whole and ragged
     token tiles sum every product over K in the same order."""
-    if c_out > 1000 and case[1] > 6000:
+    if c_out > 6000 and case[1] > 6000:
         c_out = 8200
     check_batches(case, c_out, (1, 2, 3, 4, 5, 8, 16, 17, 24, 25, 32, 33, 40, 96, 97, 128, 200))
 
