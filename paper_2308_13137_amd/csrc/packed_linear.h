@@ -14,8 +14,8 @@
 // block's four stacked linears (W g128, 4 blocks, one graph; against the vector
 // kernel at up to 7 tokens and the former matrix-core kernel above):
 //   W4, 1 token 38.4 -> 37.1 us; W3, 1 token 44.9 -> 38.1; W4, 4 tokens 66 -> 43;
-//   8 tokens 51 -> 47; 16 tokens 57 -> 49; W3, 24 tokens 80 -> 63; W2 g64 (13B),
-//   4 tokens 103 -> 66; W4, 500 tokens 1274 -> 460.
+//   8 tokens 51 -> 45; 16 tokens 57 -> 49; W3, 24 tokens 80 -> 63; W2 g64 (13B),
+//   4 tokens 103 -> 66; W4, 500 tokens 1274 -> 450.
 // Against 64-bit sums the results are 4 to 40 times closer than before (the codes'
 // offset is 2^BITS instead of 128, so less cancels).
 #pragma once
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(PM_THREADS) void packed_wide_kernel(
 // super-blocks in the order of the small-batch kernel's waves (0, 8, .., then 2,
 // 10, ..; 1, 9, ..), each wave's share summed on its own.  It costs: with xs
 // from the staging thread and K in sequence, 500 tokens through a 7B block's
-// linears at W4 took 445 us, now 460 (2048 tokens, 12288 x 4096, W3: 403 -> 446).
+// linears at W4 took 445 us, now 450 to 460 (2048 tokens, 12288 x 4096, W3: 403 -> 446).
 // Shares of contiguous super-blocks cost more in the small-batch kernel (W2 g64,
 // 4 tokens: 257 -> 300 us); sums formed by one wave for the others were no faster
 // (495 us).
@@ -1418,7 +1418,7 @@ hipError_t launch_vector(const LinArgs& a, const uint16_t* X, int n_tok, void* Y
 // until its tiles fill the chip, while the small-batch kernel pays one pass over
 // the codes per 32 tokens (a 7B block's linears as one graph, W3 g128: 96 tokens
 // 215 us in launches of 32, 97 and 128 tokens 224 us tiled; 500 tokens W4, one by
-// one: 1272 us in launches, 460 us tiled).
+// one: 1272 us in launches, 450 us tiled).
 constexpr int64_t TILE_TOKENS = 97;
 
 template <int BITS, int SUB>
