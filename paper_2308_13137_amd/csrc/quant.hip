@@ -272,7 +272,7 @@ __global__ __launch_bounds__(NT) void lwc_fwd_kernel(
 // per element: dW~ = g*m + [i = argmax] dmax + [i = argmin] dmin
 // per column (optional): partial sum over this block's rows of dW~ * W.
 template <typename TW, int KC, bool WHOLE_ROW, bool LETW, int NTB = NT>
-__global__ __launch_bounds__(NTB, WHOLE_ROW && !LETW && NTB == 512 && KC == 3 ? 4 : 1) void lwc_bwd_kernel(
+__global__ __launch_bounds__(NTB, WHOLE_ROW && !LETW && NTB == 512 && KC == 3 && sizeof(TW) == 2 ? 4 : 1) void lwc_bwd_kernel(
     const TW* __restrict__ W, int64_t c_out, int64_t c_in, const float* __restrict__ s,
     const float* __restrict__ gl, const float* __restrict__ bl, int bits, int group, int R,
     const float* __restrict__ dW, float* __restrict__ dgl, float* __restrict__ dbl,
@@ -371,16 +371,18 @@ __global__ __launch_bounds__(NTB, WHOLE_ROW && !LETW && NTB == 512 && KC == 3 ? 
       }
       const QParams p = make_group_qparams(quant, st.mx, st.mn, gl[row], bl[row], qmax);
       float2 sums = make_float2(0.f, 0.f);
-      uint32_t inside[KC];                               // the elements' clip flags
+      // the elements' clip flags, kept as bits (where LET's arrays already spill, formed again)
+      constexpr bool KEEP = !(LETW && KC >= 7);
+      uint32_t inside[KEEP ? KC : 1];
 #pragma unroll
       for (int k = 0; k < KC; ++k) {
         const int j = tid + NTB * k;
-        inside[k] = 0u;
+        if constexpr (KEEP) inside[k] = 0u;
         if (j < cpr) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const QElem qe = quant_elem(wt_at(k, e), p, qmax);
-            inside[k] |= qe.m ? 1u << e : 0u;
+            if constexpr (KEEP) inside[k] |= qe.m ? 1u << e : 0u;
             group_terms(quant, g[k][e], qe, p, qmax, sums.x, sums.y);
           }
         }
@@ -417,7 +419,10 @@ __global__ __launch_bounds__(NTB, WHOLE_ROW && !LETW && NTB == 512 && KC == 3 ? 
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const int col = 8 * j + e;
-              float x = (inside[k] >> e) & 1u ? gg[e] : 0.0f;
+              bool in;
+              if constexpr (KEEP) in = (inside[k] >> e) & 1u;
+              else in = quant_elem(wt_at(k, e), p, qmax).m;
+              float x = in ? gg[e] : 0.0f;
               if (quant == WQ_LWC) {
                 if (col == st.imx) x += qg.dmx;
                 if (col == st.imn) x += qg.dmn;
@@ -1382,6 +1387,21 @@ constexpr int64_t LWC_BLOCKS = 768;
 constexpr int64_t ACT_BLOCKS = 768;
 constexpr int64_t ROW_BLOCKS = 1 << 20;  // one block per row up to here
 
+// Whole rows with LET's arrays spill at eight chunks per thread: six or seven where
+// they reach (LWC backward with s, bf16: 2048 x 20480 360 -> 163 us, 8192 x 28672
+// 1826 -> 1373; activation backward, 333 x 28672: 198 -> 181 us, fp32 185 -> 166).
+// SEVEN: not the LWC backward of fp32 weights (8192 x 28672: 1687 -> 1914).
+template <int KC, int NTB, bool WHOLE_ROW, bool SEVEN, typename F>
+void by_width(int64_t C, F f) {
+  if constexpr (WHOLE_ROW && KC == 8 && NTB == 512) {
+    if (C / 8 <= 6 * NTB) return f(std::integral_constant<int, 6>{});
+    if constexpr (SEVEN) {
+      if (C / 8 <= 7 * NTB) return f(std::integral_constant<int, 7>{});
+    }
+  }
+  f(std::integral_constant<int, KC>{});
+}
+
 #define OQ_KC_SWITCH(KCV, ...)                      \
   switch (KCV) {                                    \
     case 1: { constexpr int KC = 1; __VA_ARGS__; } break;  \
@@ -1648,13 +1668,17 @@ hipError_t lwc_bwd(const void* W, bool w_bf16, int64_t c_out, int64_t c_in, cons
       // the ds partials are one row per block: the block count is the fixed
       // lwc_bwd_nparts(c_out) the workspace was sized for
       const int R = rows_per_block(c_out, LWC_BLOCKS);
-      hipLaunchKernelGGL((lwc_bwd_kernel<TW, KCc, WR, true, NTc>), dim3(unsigned((c_out + R - 1) / R)),
-                         dim3(NTc), 0, st, static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits,
-                         int(group), R, dW, dgl, dbl, dW_tilde, ds_parts, quant, gs);
+      by_width<KCc, NTc, WR, sizeof(TW) == 2>(c_in, [&](auto kcw) {
+        hipLaunchKernelGGL((lwc_bwd_kernel<TW, decltype(kcw)::value, WR, true, NTc>),
+                           dim3(unsigned((c_out + R - 1) / R)), dim3(NTc), 0, st,
+                           static_cast<const TW*>(W), c_out, c_in, s, gl, bl, bits, int(group), R, dW,
+                           dgl, dbl, dW_tilde, ds_parts, quant, gs);
+      });
     } else {
       // no partials: one round of resident blocks; whole rows of up to three
       // quarters of a width take that many chunks, for two blocks per compute
-      // unit (4,096 rows of 11,008: 125 -> 90 us)
+      // unit (4,096 rows of 11,008, bf16: 125 -> 90 us; fp32 weights would spill
+      // in two: 135 us in one, 146 in two)
       auto plain = [&](auto kcp) {
         constexpr int K = decltype(kcp)::value;
         const auto kernel = lwc_bwd_kernel<TW, K, WR, false, NTc>;
@@ -1801,7 +1825,7 @@ hipError_t act_bwd(const void* X, bool x_bf16, int64_t T, int64_t C, int bits, c
     constexpr int K34 = KCc >= 4 ? KCc / 4 * 3 : KCc;
     const std::integral_constant<int, NTc> nt{};
     if (let)
-      launch(tx, std::integral_constant<int, KCc>{}, nt, std::true_type{});
+      by_width<KCc, NTc, true, true>(C, [&](auto kcw) { launch(tx, kcw, nt, std::true_type{}); });
     else if (C / 8 <= K34 * NTc)
       launch(tx, std::integral_constant<int, K34>{}, nt, std::false_type{});
     else

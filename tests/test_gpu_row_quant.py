@@ -10,8 +10,8 @@ from paper_2308_13137_amd import oq
 
 pytestmark = pytest.mark.gpu
 
-# channels at and just past 1, 2, 3, 4 chunks of 256 threads and 3, 4, 6 of 512
-WIDTHS = (64, 2048, 2056, 4096, 6144, 6152, 8192, 8200, 12288, 12296, 16384, 24576, 24584)
+# channels at and just past 1, 2, 3, 4 chunks of 256 threads and 3, 4, 6, 7 of 512
+WIDTHS = (64, 2048, 2056, 4096, 6144, 6152, 8192, 8200, 12288, 12296, 16384, 16392, 24576, 24584, 28672, 28680)
 
 
 def bits_equal(a, b):
