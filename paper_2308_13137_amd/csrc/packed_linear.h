@@ -1328,8 +1328,9 @@ hipError_t launch_mfma(const LinArgs& a, const uint16_t* X, int n_tok, void* Y) 
 // activations dearer (12 tokens: 12.9 -> 12.3 us), or 4096 where two parts per
 // block double that work (W2 g64, 4 tokens, 5120 rows: 11.1 -> 9.7 us); fewer
 // rows measured slower (4096 rows, g128, one token: 6.0 -> 7.2 us).  One token
-// leaves little to share and takes one tile, except at 3 bits (44032 x 8192: W4
-// 46.6 -> 42.1 us, W6 67.7 -> 59.2, W2 35.5 -> 33.2; W3 42.7 with two, 44.5 with one).
+// leaves little to share and takes one tile (44032 x 8192: W4 46.6 -> 42.1 us, W6 67.7
+// -> 59.2, W2 35.5 -> 33.2), except at 3 bits (42.7 with two, 44.5 with one) and at
+// most 4096 channels of up to 4 bits (22016 x 4096, W4: 14.6 with two, 14.9 with one).
 // 5 to 8 tokens have rings of their own (12288 x 4096, W4, 8 tokens: 14.3 us in rings
 // of 16 tokens, 11.7 in rings of 8; two tiles 13.1; 13824 x 5120: one 17.8, two 16.4).
 // The rings are two units deep: deeper ones cost
@@ -1341,7 +1342,7 @@ hipError_t launch_mfma_rt(const LinArgs& a, const uint16_t* X, int n_tok, void* 
     if (a.c_in % PM_BLOCK) return launch_mfma<BITS, TT, 1, SUB, 2, false>(a, X, n_tok, Y);
   }
   if constexpr (TT < 32 && MfmaCfg<BITS, TT, 2, SUB>::FITS) {
-    const bool one = TT == 4 && SUB == 1 && BITS != 3 && n_tok == 1;
+    const bool one = TT == 4 && SUB == 1 && n_tok == 1 && (BITS >= 5 || (BITS != 3 && a.c_in > 4096));
     const int64_t from = SUB == 2 ? 4096 : TT == 4 ? 16384 : TT == 8 ? 13312 : TT == 16 ? 12288 : 8192;
     if (!one && a.c_out >= from && MfmaCfg<BITS, TT, 2, SUB>::lds(2, a.c_in, n_tok, a.bias != nullptr) <= PL_LDS_MAX)
       return launch_mfma<BITS, TT, 2, SUB, 2, true>(a, X, n_tok, Y);
